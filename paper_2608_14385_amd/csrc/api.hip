@@ -272,39 +272,53 @@ int down_ks_of(const deamoe_config &c, int T) {
 
 // Down projections and combine fused into one kernel (the SLICE down stage,
 // the FACTORED department down stage): batches whose active units fit the
-// kernel's unit table.  Its grid is one workgroup per 32 rows of y.  SLICE:
-// up to 32 tokens (two token tiles from 17 on); below kChainMinTiles row
-// pairs (a hidden size under 4096, where the kernel takes 16-row blocks) up
-// to kChainNarrowMaxT tokens from kChainNarrowMinTiles row pairs on
-// (same-process A/B on the 2048-wide 7B-class layer against the separate
-// down stage and combine, us per step: 66.5 -> 61.5 at 5 tokens, 81.0 ->
-// 76.1 at 16, 89.6 -> 85.6 at 24, but 89.9 -> 91.1 at 32), and up to 4
-// tokens on narrower layers, where the kernel's workgroups leave most CUs
-// idle (the 1024-wide Baseline-7B vanilla layer, separate stage against the
-// fused kernel: 58.9 -> 46.5 at 8 tokens, 88.6 -> 64.5 at 16).  FACTORED: up to 16 tokens at every Table 1 width (at
-// least kChainMinTilesFactored row pairs, h >= 1024): the fused kernel saves
-// the combine launch.  Same-process A/B against the separate department down
-// stage and combine, us per step: Baseline-7B (h = 1024) 38.3 -> 36.3 at one
-// token, 77.7 -> 75.6 at 16; Qwen3 (h = 4096, with 16-row blocks) 79.8 ->
-// 76.9 at one token, 220.7 -> 214.4 at 8, 308.2 -> 305.1 at 16; DeepSeek-V2
-// (h = 5120) 90.3 -> 86.6 at one token, 389.7 -> 389.0 at 16.
+// kernel's unit table.  SLICE: up to 32 tokens (two token tiles from 17 on),
+// below kChainMinTiles row pairs (a hidden size under 4096) up to
+// kChainNarrowMaxT.  There the fused kernel measured faster beyond, too (the
+// 2048-wide 7B-class layer 85.3 -> 77.0 us per step at 25 tokens, 85.5 ->
+// 81.5 at 32), but the traced call gives those batches a boundary between the
+// down stage and the combine, which callers count.  On layers under
+// kChainNarrowMinTiles row pairs (2048), whose few workgroups must each walk
+// every unit, only up to 4 tokens or while the step has at most
+// kChainNarrowSteps K steps.  Same-process A/B against the separate down
+// stage and combine, us per step: the 256-wide fp32 layer (at most 48 steps)
+// 38.9 -> 26.2 at 6 tokens, 41.3 -> 29.3 at 16; the 1024-wide Baseline-7B
+// vanilla layer even at 5 (at most 120 steps), 46.7 -> 49.5 at 8 (192) and
+// 65.2 -> 71.2 at 16.  FACTORED: up to 16 tokens at every
+// Table 1 width (at least kChainMinTilesFactored row pairs, h >= 1024): the
+// fused kernel saves the combine launch.  Same-process A/B against the
+// separate department down stage and combine, us per step: Baseline-7B (h =
+// 1024) 38.3 -> 36.3 at one token, 77.7 -> 75.6 at 16; Qwen3 (h = 4096) 79.8
+// -> 76.9 at one token, 220.7 -> 214.4 at 8, 308.2 -> 305.1 at 16;
+// DeepSeek-V2 (h = 5120) 90.3 -> 86.6 at one token, 389.7 -> 389.0 at 16.
 constexpr int kChainMinTiles = 128, kChainMinTilesFactored = 32;
-constexpr int kChainNarrowMinTiles = 64, kChainNarrowMaxT = 24;
+constexpr int kChainNarrowMinTiles = 64, kChainNarrowMaxT = 24, kChainNarrowSteps = 96;
+// Units (and SLICE K steps) of the fused kernel a step of T tokens can have
+// at most.
+struct ChainBound {
+  int units, steps;
+};
+ChainBound chain_bound(const deamoe_config &c, int T) {
+  const int dk = std::min(c.top_k_dept > 0 ? c.top_k_dept : c.top_k, std::min(c.top_k, c.n_depts));
+  const bool slice_priv = c.form == DEAMOE_FORM_SLICE && c.d_private > 0;
+  const int depts = std::min(c.n_depts, T * dk);
+  const int exps = slice_priv ? std::min(c.n_experts, T * c.top_k) : 0;
+  const int ks = kstep_of(c.w_dtype);
+  return {depts + exps + (c.d_shared_expert ? 1 : 0),
+          depts * (c.d_shared / ks) + exps * (c.d_private / ks) + c.d_shared_expert / ks};
+}
 bool use_chain(const deamoe_config &c, int T) {
   if (T > kChainT) return false;
   // the plan builds the fused kernel's units for one token group only
   if (token_groups_max(c, T) > 1) return false;
   const int tiles = c.hidden / (2 * kTile);
   if (c.form == DEAMOE_FORM_FACTORED && (T > kTile || tiles < kChainMinTilesFactored)) return false;
-  if (c.form == DEAMOE_FORM_SLICE && tiles < kChainMinTiles &&
-      T > (tiles >= kChainNarrowMinTiles ? kChainNarrowMaxT : 4))
-    return false;
-  const int dk = std::min(c.top_k_dept > 0 ? c.top_k_dept : c.top_k, std::min(c.top_k, c.n_depts));
-  const bool slice_priv = c.form == DEAMOE_FORM_SLICE && c.d_private > 0;
-  const int units = std::min(c.n_depts, T * dk) +
-                    (slice_priv ? std::min(c.n_experts, T * c.top_k) : 0) +
-                    (c.d_shared_expert ? 1 : 0);
-  return units <= kMaxChainUnits;
+  const ChainBound b = chain_bound(c, T);
+  if (c.form == DEAMOE_FORM_SLICE) {
+    if (tiles < kChainMinTiles && T > kChainNarrowMaxT) return false;
+    if (tiles < kChainNarrowMinTiles && T > 4 && b.steps > kChainNarrowSteps) return false;
+  }
+  return b.units <= kMaxChainUnits;
 }
 
 // Upper bound of the row tiles of a stage, for the grid size.
@@ -551,6 +565,7 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       ch.T = T;
       ch.h = c.hidden;
       ch.act_f32 = c.act_dtype == DEAMOE_F32;
+      ch.max_units = chain_bound(c, T).units;
       DEAMOE_TRY(launch_chain(ch, wt, s));
       DEAMOE_TRY(ev.mark());
       return DEAMOE_OK;
@@ -607,6 +622,7 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       ch.T = T;
       ch.h = c.hidden;
       ch.act_f32 = c.act_dtype == DEAMOE_F32;
+      ch.max_units = chain_bound(c, T).units;
       DEAMOE_TRY(launch_chain(ch, wt, s));
       DEAMOE_TRY(ev.mark());
       return DEAMOE_OK;

@@ -10,10 +10,10 @@
 // (P_{t,j} for a department, Sec. 3.2), one product over the concatenated K
 // steps of all units in which token t's column carries the weight p_{t,u}
 // and zero for units it does not use.  A workgroup owns 32 rows of y (two
-// 16-row halves sharing the token operand; 16 rows on narrow layers) and
-// splits the concatenated K
-// steps into KSC contiguous ranges, one per wave, so that every wave streams
-// one long run of weight rows; each K step's product is added to the
+// 16-row halves sharing the token operand; 16 or 8 rows on narrow layers) and
+// splits the concatenated K steps into KSC contiguous ranges, one per wave,
+// so that every wave streams one long run of weight rows; each K step's
+// product is added to the
 // accumulator with the lane's token weight (times the fp8 block scale), and
 // the partial tiles are summed through LDS in wave order and rounded once.
 // No fp32 partial rows and no combine launch.  The FACTORED department down
@@ -50,41 +50,46 @@ __device__ inline void chain_mma(const u32x4 (&a)[NW][4], const u32x4 (&b)[4], f
   }
 }
 
-// A 64-bit pointer every lane holds alike, moved to scalar registers.
-template <class P>
-__device__ inline P *uniform_ptr(P *p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<P *>(((uint64_t)hi << 32) | lo);
-}
-
 // NW: 16-row halves of y per workgroup (1 or 2; two share the token operand).
-template <int WT, int NW, int NTT, int KSC, int PF>
+// Bound by the read rate on wide layers (224 workgroups at 7168: 6.7 TB/s at
+// 16 tokens), by a CU's rate and the prologue on narrow ones.  Scalar step
+// addresses, the unit fields through scalar loads instead of LDS and one loop
+// exit took the pair kernel from 170 registers to 146 (three waves per SIMD);
+// kernel time by trace, us: the DeepSeek-V3 shape 174.9 -> 171.9 at 16
+// tokens, 214.5 -> 212.4 at 32, fp8 142.1 -> 135.3 at 32 and 20.5 -> 19.7 at
+// one token, the 256-wide fp32 layer 7.4 -> 5.7 at 4.
+// P: with NW == 1, a load group is P K steps of 16 / P rows instead of one
+// step of 16 rows: the same 16-row segments in flight, in P times the
+// workgroups.  A matrix-core tile then holds the rows P times over.
+template <int WT, int NW, int P, int NTT, int KSC>
 __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
+  static_assert(P == 1 || NW == 1, "K steps side by side only in one half");
   using Tr = WTraits<WT>;
   using LD = WLoad<WT>;
-  constexpr int TR = NW * kTile;   // rows of y per workgroup
-  constexpr int NB = PF + 1;       // load groups per wave: PF in flight, one multiplied
+  static_assert(LD::NQ % P == 0, "a K step is a whole number of load instructions");
+  constexpr int SR = kTile / P;    // rows of a K step
+  constexpr int TR = NW * SR;      // rows of y per workgroup
+  constexpr int QS = LD::NQ / P;   // load instructions of a K step and half
   constexpr int ASEG = Tr::K_STEP * Tr::A_BYTES;
   constexpr int STAGE = NW * LD::REGION;
   constexpr int RED = NW * NTT * kWave * 16;
   constexpr int WB = STAGE > RED ? STAGE : RED;
   __shared__ __attribute__((aligned(16))) char s_buf[KSC][WB];
-  __shared__ ChainUnit s_u[kMaxChainUnits];
-  const int n_units = uniform(a.counts[0]), S = uniform(a.counts[1]);
-  {
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(a.units);
-    uint32_t *dst = reinterpret_cast<uint32_t *>(s_u);
-    const int nd = n_units * (int)(sizeof(ChainUnit) / 4);
-    for (int i = threadIdx.x; i < nd; i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
   const int wave = uniform(threadIdx.x / kWave), lane = lane_id();
   const int g = lane >> 4, j = lane & 15;
   const int T = a.T, R = a.h, rt = blockIdx.x;
   const int lrow = lane / LD::LPR, lchunk = lane % LD::LPR;
-  const int rmax = R - 1 - (NW - 1) * kTile;   // last row the first half may read
+  // Where the wave's range starts: every lane counts the units that begin at
+  // or before it.  As many entries are read as the batch can have units, not
+  // as it has, so that the table's loads don't wait for the counts'.
+  int step0[kMaxChainUnits / kWave];
+#pragma unroll
+  for (int i = 0; i < kMaxChainUnits / kWave; ++i) {
+    step0[i] = 0;
+    if (i * kWave < a.max_units)
+      step0[i] = glob(a.units)[min(i * kWave + lane, a.max_units - 1)].step0;
+  }
+  const int n_units = uniform(a.counts[0]), S = uniform(a.counts[1]);
   const int s_lo = uniform((int)((int64_t)S * wave / KSC));
   const int total = uniform((int)((int64_t)S * (wave + 1) / KSC)) - s_lo;
   char *lds = s_buf[wave];
@@ -95,101 +100,119 @@ __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt) acc[n][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
   if (total > 0) {
-    // the unit holding step s_lo: the last one whose first step is <= s_lo
-    int lo = 0, hi = n_units - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (uniform(s_u[mid].step0) <= s_lo) lo = mid; else hi = mid - 1;
-    }
-    int cu = uniform(lo);
-    // issue cursor: unit cu, its K step ck of nk; the unit's per-lane state
-    int ck = s_lo - uniform(s_u[cu].step0), nk = 0, ldw = 0;
-    const char *w0 = nullptr, *bp[NTT];
-    const float *sp = nullptr, *pp[NTT];
-    uint64_t mm[NTT];   // per token tile: lanes whose token is a member of the unit
+    int cu = -1;   // the unit holding step s_lo: the last one that begins by then
+#pragma unroll
+    for (int i = 0; i < kMaxChainUnits / kWave; ++i)
+      if (i * kWave < a.max_units)
+        cu += __popcll(__ballot(i * kWave + lane < n_units && step0[i] <= s_lo));
+    // issue cursor: K step ck of nk of unit cu.  Every address is a scalar
+    // base, moved per step, plus a 32-bit lane offset, set per unit: a step's
+    // loads cost one scalar addition each.  The next unit's fields are loaded
+    // while this one streams.
+    const auto *units = reinterpret_cast<const __attribute__((address_space(4))) ChainUnit *>(
+        reinterpret_cast<uintptr_t>(a.units));
+    ChainUnit nu;
+    auto fetch = [&](int u) {
+      const auto *p = units + min(u, n_units - 1);
+      nu.w = p->w; nu.s = p->s; nu.in = p->in; nu.pw = p->pw; nu.K = p->K; nu.mask = p->mask;
+      nu.step0 = p->step0;
+    };
+    fetch(cu);
+    int ck = s_lo - nu.step0 - 1, nk = 0;
+    const char *wb = nullptr, *in = nullptr;   // this tile's rows; the unit's token rows
+    const float *sp = nullptr, *pw = nullptr;
+    uint32_t wq = 0, wvo = 0, bvo[NTT];        // wq: bytes from one load instruction's rows to the next
+    uint32_t m32 = 0;
     const uint32_t tmask = T >= 32 ? 0xffffffffu : (1u << T) - 1u;
-    auto load_unit = [&](int u) {
-      ldw = uniform(s_u[u].K);
-      nk = ldw / Tr::K_STEP;
-      w0 = static_cast<const char *>(uniform_ptr(s_u[u].w)) + lchunk * 16;
-      const uint32_t m32 = (uint32_t)uniform((int)s_u[u].mask) & tmask;
-      const char *in = static_cast<const char *>(uniform_ptr(s_u[u].in));
-      const float *pw = uniform_ptr(s_u[u].pw);
+    auto next_unit = [&]() {
+      const int K = nu.K;
+      nk = K / Tr::K_STEP;
+      wb = static_cast<const char *>(nu.w) + (size_t)(rt * TR) * K * Tr::W_BYTES;
+      wq = (uint32_t)LD::RPI * K * Tr::W_BYTES;
+      wvo = (uint32_t)lrow * K * Tr::W_BYTES + lchunk * 16;
+      m32 = nu.mask & tmask;
+      in = static_cast<const char *>(nu.in);
+      pw = nu.pw;
 #pragma unroll
       for (int tt = 0; tt < NTT; ++tt) {
-        const uint32_t m16 = (m32 >> (kTile * tt)) & 0xffffu;
-        mm[tt] = (uint64_t)m16 * 0x0001000100010001ull;
         // a member's row is its rank among the members; other lanes read the
         // first member's row (their weight is zero), so each load touches
         // only the unit's rows
         const int tok = kTile * tt + j;
-        const int rank = (m16 >> j) & 1 ? __popc(m32 & ((1u << tok) - 1u)) : 0;
-        bp[tt] = in + (size_t)rank * ldw * Tr::A_BYTES;
-        pp[tt] = pw + tok;
+        const int rank = (m32 >> tok) & 1 ? __popc(m32 & ((1u << tok) - 1u)) : 0;
+        bvo[tt] = (uint32_t)rank * K * Tr::A_BYTES + b_chunk_offset(g, 0);
       }
-      if constexpr (WT == WT_FP8)   // the tile's 32 rows lie in one scale row
-        sp = uniform_ptr(s_u[u].s) + (size_t)((rt * TR) / 128) * (ldw / 128);
+      if constexpr (WT == WT_FP8)   // the tile's rows lie in one scale row
+        sp = nu.s + (size_t)((rt * TR) / 128) * (K / 128);
+      fetch(++cu);
     };
-    load_unit(cu);
-    // loads past the wave's range read cache-resident data of the first unit
-    const char *dummy = bp[0] + (lane & 15) * 16;
-    const char *dummy_b = bp[0];
-    const float *dummy_s = sp, *dummy_p = pp[0];
-    u32x4 G[NB][NW][LD::NQ];
-    u32x4 B[NB][NTT][4];
-    uint64_t MM[NB][NTT];
-    float SC[NB], P[NB][NTT];
-    auto issue = [&](u32x4(&Gb)[NW][LD::NQ], u32x4(&Bb)[NTT][4], uint64_t(&mms)[NTT], float &sc,
-                     float(&pw)[NTT], int v) {
-      const bool ok = v < total;
-      if (ok && ck == nk) {   // the previous step ended a unit
-        ++cu;
-        ck = 0;
-        load_unit(cu);
-      }
+    next_unit();
+    u32x4 G[2][NW][LD::NQ];   // one load group in flight, one multiplied
+    u32x4 B[2][P][NTT][4];
+    uint32_t MM[2][P];        // the step's member tokens, none past the wave's range
+    float SC[2][P], PW[2][P][NTT];
+    // the loads of the wave's steps v .. v + P - 1 (past the range: the last
+    // step's again, which are cached, with weight zero)
+    auto issue = [&](int q, int v) {
 #pragma unroll
-      for (int q = 0; q < LD::NQ; ++q) {
-        const int row = min(rt * TR + q * LD::RPI + lrow, rmax);
-        const size_t woff = (size_t)row * ldw * Tr::W_BYTES + (size_t)ck * LD::WSEG;
-        const size_t half = (size_t)kTile * ldw * Tr::W_BYTES;
-        Gb[0][q] = __builtin_nontemporal_load(gptr(ok ? w0 + woff : dummy));
-        if constexpr (NW == 2)
-          Gb[1][q] = __builtin_nontemporal_load(gptr(ok ? w0 + woff + half : dummy));
-      }
+      for (int p = 0; p < P; ++p) {
+        if (v + p < total) {
+          if (++ck == nk) {
+            ck = 0;
+            next_unit();
+          }
+          MM[q][p] = m32;
+        } else {
+          MM[q][p] = 0;
+        }
 #pragma unroll
-      for (int tt = 0; tt < NTT; ++tt) {
-        const char *b = ok ? bp[tt] + (size_t)ck * ASEG : dummy_b;
+        for (int i = 0; i < QS; ++i) {
+          const char *base = wb + (size_t)ck * LD::WSEG + (size_t)i * wq;
+          G[q][0][p * QS + i] = __builtin_nontemporal_load(gptr(base + wvo));
+          if constexpr (NW == 2)
+            G[q][1][i] = __builtin_nontemporal_load(gptr(base + (size_t)QS * wq + wvo));
+        }
+        const char *bb = in + (size_t)ck * ASEG;
+        // two steps of one unit load the same token weights: kept two loads,
+        // as one would be copied, and so waited for, where they are issued
+        const float *pws = pw;
+        asm("" : "+s"(pws));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) Bb[tt][q] = *gptr(b + b_chunk_offset(g, q));
-        pw[tt] = *gfptr(ok ? pp[tt] : dummy_p);
-        mms[tt] = mm[tt];
+        for (int tt = 0; tt < NTT; ++tt) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) B[q][p][tt][i] = *gptr(bb + bvo[tt] + b_chunk_offset(0, i));
+          PW[q][p][tt] = *gfptr(pws + (uint32_t)(kTile * tt + j));
+        }
+        if constexpr (WT == WT_FP8) SC[q][p] = *gfptr(sp + ck);
       }
-      if constexpr (WT == WT_FP8) sc = *gfptr(ok ? sp + ck : dummy_s);
-      if (ok) ++ck;
     };
+    auto multiply = [&](int q) {
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 w[P][NW][4];
+      stage_weights<WT, NW, P>(lds, G[q], w);
 #pragma unroll
-    for (int p = 0; p < PF; ++p) issue(G[p], B[p], MM[p], SC[p], P[p], p);
-    for (int v = 0;;) {
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        const int qn = (q + NB - 1) % NB;   // the buffer consumed one step ago
-        issue(G[qn], B[qn], MM[qn], SC[qn], P[qn], v + PF);
-        __builtin_amdgcn_sched_barrier(0);
-        u32x4 w[NW][4];
-        stage_weights<WT, NW>(lds, G[q], w);
+      for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int tt = 0; tt < NTT; ++tt) {
           // tokens outside the unit have weight zero (their operand is a
           // member's row, so the product is finite)
-          const float f0 = (MM[q][tt] >> lane) & 1 ? P[q][tt] : 0.f;
-          chain_mma<WT, NW>(w, B[q][tt], WT == WT_FP8 ? f0 * SC[q] : f0, acc, tt);
+          const float f0 = (MM[q][p] >> (kTile * tt + j)) & 1 ? PW[q][p][tt] : 0.f;
+          chain_mma<WT, NW>(w[p], B[q][p][tt], WT == WT_FP8 ? f0 * SC[q][p] : f0, acc, tt);
         }
-        __builtin_amdgcn_sched_barrier(0);
-        if (++v >= total) goto streamed;
-      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // one exit, in the middle: with more, the compiler peels a first round
+    // and waits for its loads to copy their registers
+    issue(0, 0);
+    for (int v = 0;; v += 2 * P) {
+      issue(1, v + P);
+      multiply(0);
+      if (v + 2 * P >= total) break;
+      issue(0, v + 2 * P);
+      multiply(1);
     }
+    multiply(1);
   }
-streamed:
   // partial tiles summed in wave order; wave 0 rounds and stores
   __syncthreads();   // every wave is done with its staging region
   f32x4 *red = reinterpret_cast<f32x4 *>(s_buf[wave]);
@@ -208,6 +231,7 @@ streamed:
 #pragma unroll
         for (int tt = 0; tt < NTT; ++tt) acc[n][tt] += r[(n * NTT + tt) * kWave + lane];
     }
+    if (4 * g >= SR) return;   // the rows' copies
     const int row0 = rt * TR + 4 * g, row1 = row0 + kTile;
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt) {
@@ -222,13 +246,14 @@ streamed:
   }
 }
 
-template <int WT, int NW, int NTT>
+template <int WT, int NW, int P, int NTT>
 static hipError_t launch_chain_wt(const ChainArgs &a, hipStream_t s) {
-  const dim3 grid((a.h + NW * kTile - 1) / (NW * kTile));
+  constexpr int TR = NW * kTile / P;
   // 8 waves per workgroup, each streaming one contiguous range of the
   // concatenated K steps, one load group in flight while one is multiplied
-  constexpr int KSC = 8, PF = 1;
-  hipLaunchKernelGGL((chain_down_kernel<WT, NW, NTT, KSC, PF>), grid, dim3(KSC * kWave), 0, s, a);
+  constexpr int KSC = 8;
+  hipLaunchKernelGGL((chain_down_kernel<WT, NW, P, NTT, KSC>), dim3((a.h + TR - 1) / TR),
+                     dim3(KSC * kWave), 0, s, a);
   return hipGetLastError();
 }
 
@@ -241,12 +266,24 @@ static hipError_t launch_chain_wt(const ChainArgs &a, hipStream_t s) {
 // 389.0 -> 393.5 at 16) and at the 7168-wide DeepSeek-V3 shape (108.3 ->
 // 110.4 us at one token, 525.4 -> 546.7 at 16) single halves were slower.
 constexpr int kChainPairMinH = 5120;
+// Up to 2048, where 16-row blocks leave half the CUs idle, a workgroup takes
+// 8 rows, two K steps side by side in a load group (at most 256 workgroups of
+// one a CU).  A CU's own rate is what bounds the kernel there, not the
+// latency: 12 or 16 waves on 128 CUs were no faster.  Kernel time by trace,
+// us, 16 rows -> 8: the 7B-class layer 10.0 -> 8.4 at one token, 16.4 -> 13.7
+// at 5, 22.2 -> 18.6 at 16, 29.5 -> 26.9 at 24; Baseline-7B (1024 wide) 6.3
+// -> 5.5 at 16, 4.6 -> 5.2 at one token.  At 4096 (Qwen3, 512 workgroups in
+// two rounds) 8 rows lost: 18.9 -> 25.2 at 16, and 4 rows lost at 2048 too.
+constexpr int kChainSplitMaxH = 2048;
 
 template <int WT>
 static hipError_t launch_chain_ntt(const ChainArgs &a, hipStream_t s) {
+  const bool one = a.T <= kTile;
+  if (a.h <= kChainSplitMaxH)
+    return one ? launch_chain_wt<WT, 1, 2, 1>(a, s) : launch_chain_wt<WT, 1, 2, 2>(a, s);
   if (a.h < kChainPairMinH)
-    return a.T > kTile ? launch_chain_wt<WT, 1, 2>(a, s) : launch_chain_wt<WT, 1, 1>(a, s);
-  return a.T > kTile ? launch_chain_wt<WT, 2, 2>(a, s) : launch_chain_wt<WT, 2, 1>(a, s);
+    return one ? launch_chain_wt<WT, 1, 1, 1>(a, s) : launch_chain_wt<WT, 1, 1, 2>(a, s);
+  return one ? launch_chain_wt<WT, 2, 1, 1>(a, s) : launch_chain_wt<WT, 2, 1, 2>(a, s);
 }
 
 hipError_t launch_chain(const ChainArgs &a, int wtype, hipStream_t s) {

@@ -179,12 +179,14 @@ __device__ inline void step_mma(const u32x4 (&a)[NW][4], const u32x4 (&B)[NTT][S
 // Rows of one staged K step (as loaded: instruction q covers rows
 // q * RPI + lane / LPR, 16 bytes each) written to the wave's LDS region and
 // read back in the matrix-core operand layout.
-template <int WT, int NW>
+// P: the region holds P K steps of 16 / P rows each (step p's rows from
+// p * 16 / P on); operand lane j takes row j % (16 / P).
+template <int WT, int NW, int P>
 __device__ inline void stage_weights(char *lds, const u32x4 (&Gb)[NW][WLoad<WT>::NQ],
-                                     u32x4 (&a)[NW][4]) {
+                                     u32x4 (&a)[P][NW][4]) {
   using LD = WLoad<WT>;
   const int lane = lane_id();
-  const int g = lane >> 4, j = lane & 15;
+  const int g = lane >> 4, j = lane & (kTile / P - 1);
   const int lrow = lane / LD::LPR, lchunk = lane % LD::LPR;
 #pragma unroll
   for (int n = 0; n < NW; ++n)
@@ -194,18 +196,24 @@ __device__ inline void stage_weights(char *lds, const u32x4 (&Gb)[NW][WLoad<WT>:
                                  lchunk * 16) = Gb[n][q];
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int n = 0; n < NW; ++n)
+  for (int p = 0; p < P; ++p)
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      if constexpr (WT == WT_FP8) {
-        const u32x2 v = *reinterpret_cast<const u32x2 *>(lds + n * LD::REGION + j * LD::RS +
-                                                           m * 32 + g * 8);
-        a[n][m] = u32x4{v[0], v[1], 0u, 0u};
-      } else {
-        a[n][m] = *reinterpret_cast<const u32x4 *>(lds + n * LD::REGION + j * LD::RS +
-                                                      b_chunk_offset(g, m));
+    for (int n = 0; n < NW; ++n)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const char *row = lds + n * LD::REGION + (p * (kTile / P) + j) * LD::RS;
+        if constexpr (WT == WT_FP8) {
+          const u32x2 v = *reinterpret_cast<const u32x2 *>(row + m * 32 + g * 8);
+          a[p][n][m] = u32x4{v[0], v[1], 0u, 0u};
+        } else {
+          a[p][n][m] = *reinterpret_cast<const u32x4 *>(row + b_chunk_offset(g, m));
+        }
       }
-    }
+}
+template <int WT, int NW>
+__device__ inline void stage_weights(char *lds, const u32x4 (&Gb)[NW][WLoad<WT>::NQ],
+                                     u32x4 (&a)[NW][4]) {
+  stage_weights<WT, NW, 1>(lds, Gb, reinterpret_cast<u32x4(&)[1][NW][4]>(a));
 }
 
 // Stream one work item: row tiles rt0 .. rt0 + nsub - 1 of unit U, each over

@@ -87,6 +87,7 @@ struct ChainArgs {
   const int32_t *counts;    // [0] = number of units, [1] = K steps of the concatenation
   void *y;                  // [T, h] act dtype
   int32_t T, h, act_f32;
+  int32_t max_units;        // the most units a step of T tokens can have (<= kMaxChainUnits)
 };
 
 struct ZsumArgs {

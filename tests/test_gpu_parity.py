@@ -150,6 +150,30 @@ def test_fused_down_combine(variant):
     check_case(case, baseline=baseline)
 
 
+@pytest.mark.parametrize("hidden,w_dtype,T", [
+    (2048, "bf16", 1), (2048, "bf16", 16), (2048, "bf16", 17), (2048, "bf16", 24),
+    (2048, "fp8", 3), (2048, "fp8", 23), (1024, "f32", 4), (2048, "f32", 21),
+    (256, "bf16", 16), (2176, "bf16", 19), (2176, "fp8", 7), (4096, "f32", 2)])
+def test_fused_down_row_blocks(hidden, w_dtype, T):
+    """The fused down kernel's row blocks: 8 rows with two K steps side by
+    side up to 2048, single 16-row halves from there.  Both token tiles, step
+    counts that leave waves without work (one unit of one step per expert at
+    T = 1) and ranges of odd length, a ragged shared expert."""
+    act = "f32" if w_dtype == "f32" else "bf16"
+    cfg = small(hidden=hidden, w_dtype=w_dtype, act_dtype=act, d_shared=384, d_private=128,
+                d_shared_expert=0 if T == 1 else 640, n_experts=24, top_k=3)
+    check_case(Case(cfg, T, seed=60 + T))
+
+
+@pytest.mark.parametrize("d_shared,T", [(640, 6), (1088, 5), (1152, 5)])
+def test_fused_down_narrow_steps(d_shared, T):
+    """Layers narrower than 2048 above 4 tokens: fused while a step has at
+    most 96 K steps (640: 56 at 6 tokens; 1088 and 1152: 83 and 87 at 5), the
+    separate stage beyond (d_private 512 below)."""
+    check_case(Case(small(d_shared=d_shared, d_private=64, d_shared_expert=256), T, seed=70))
+    check_case(Case(small(d_shared=d_shared, d_private=512, top_k=3), T, seed=71))
+
+
 @pytest.mark.parametrize("variant", ["f32_t128_se", "bf16_t128_se"])
 def test_four_token_tiles(variant):
     """Above 64 tokens on layers at least 4096 wide the gate/up stage holds
