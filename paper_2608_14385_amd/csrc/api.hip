@@ -78,7 +78,9 @@ Layout make_layout(const deamoe_config &c) {
   L.exp_offset = take((n + 1) * 4);
   L.exp_tokens = take(T * k * 4);
   L.counts = take(sizeof(PlanCounts));
-  for (int s = 0; s < kMaxStages; ++s) L.units[s] = take((size_t)L.max_units * sizeof(GemmUnit));
+  // units, then the prefix of their work items
+  for (int s = 0; s < kMaxStages; ++s)
+    L.units[s] = take((size_t)L.max_units * (sizeof(GemmUnit) + sizeof(int32_t)));
   const size_t S = max_slots_of(c);
   L.slot_pair = take(T * S * 4);
   L.slot_w = take(T * S * 4);
@@ -538,9 +540,11 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
   }
   const int ntt = wave_ntt_of(c, T), groups = token_groups_max(c, T);
   const PlanCounts *pc = at<PlanCounts>(ws, L.counts);
-  auto stage = [&](int i) {
+  auto stage = [&](int i, int max_units) {
     GemmStage st;
     st.units = at<GemmUnit>(ws, L.units[i]);
+    st.begin = reinterpret_cast<const int32_t *>(st.units + L.max_units);
+    st.max_units = max_units;
     st.counts = pc->stage[i];
     st.sigma = c.sigma;
     return st;
@@ -550,11 +554,12 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
   const int act_exps = std::min(c.n_experts, T * c.top_k);
   const int se = c.d_shared_expert > 0 ? 1 : 0;
   if (slice) {
+    const int units = act_depts + (c.d_private ? act_exps : 0) + se;
     const int ta = tiles_bound(act_depts, c.d_shared) +
                    (c.d_private ? tiles_bound(act_exps, c.d_private) : 0) +
                    se * tiles_bound(1, c.d_shared_expert);
     if (!small)
-      DEAMOE_TRY(launch_grouped_gemm(stage(0), wt, 2, GEMM_PLAIN, ntt, slice_gate_up_ks_of(T),
+      DEAMOE_TRY(launch_grouped_gemm(stage(0, units), wt, 2, GEMM_PLAIN, ntt, slice_gate_up_ks_of(T),
                                      ta * groups, kGridCap, s, c.hidden < 4096));
     DEAMOE_TRY(ev.mark());
     if (use_chain(c, T)) {   // down projections and combine in one kernel
@@ -570,15 +575,14 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       DEAMOE_TRY(ev.mark());
       return DEAMOE_OK;
     }
-    const int units = act_depts + (c.d_private ? act_exps : 0) + se;
-    DEAMOE_TRY(launch_down(stage(1), wt, down_ntt_of(c, T), down_groups_max(c, T),
+    DEAMOE_TRY(launch_down(stage(1, units), wt, down_ntt_of(c, T), down_groups_max(c, T),
                            down_ks_of(c, T), units, c.hidden, kGridCap, s));
     DEAMOE_TRY(ev.mark());
   } else {
     const int d = c.d_shared;
     const int t0 = tiles_bound(act_depts, d) + se * tiles_bound(1, c.d_shared_expert);
     if (!small)
-      DEAMOE_TRY(launch_grouped_gemm(stage(0), wt, 2, GEMM_PLAIN, ntt, kFactoredGateUpKs, t0 * groups,
+      DEAMOE_TRY(launch_grouped_gemm(stage(0, act_depts + se), wt, 2, GEMM_PLAIN, ntt, kFactoredGateUpKs, t0 * groups,
                                      kGridCap, s));
     if (c.sigma == DEAMOE_SIGMA_RMSNORM) {   // timed with stage 0
       RowNormArgs na;
@@ -590,11 +594,11 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       DEAMOE_TRY(launch_rownorm(na, T * dk, s));
     }
     DEAMOE_TRY(ev.mark());
-    DEAMOE_TRY(launch_grouped_gemm(stage(1), wt, 2, GEMM_SPLIT, ntt,
+    DEAMOE_TRY(launch_grouped_gemm(stage(1, act_exps), wt, 2, GEMM_SPLIT, ntt,
                                    factored_priv_ks_of(c, T), tiles_bound(act_exps, d) * groups,
                                    kGridCap, s));
     DEAMOE_TRY(ev.mark());
-    DEAMOE_TRY(launch_down(stage(2), wt, down_ntt_of(c, T), down_groups_max(c, T),
+    DEAMOE_TRY(launch_down(stage(2, act_exps), wt, down_ntt_of(c, T), down_groups_max(c, T),
                            down_ks_of(c, T), act_exps, d, kGridCap, s));
     DEAMOE_TRY(ev.mark());
     ZsumArgs za;
@@ -627,7 +631,7 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       DEAMOE_TRY(ev.mark());
       return DEAMOE_OK;
     }
-    DEAMOE_TRY(launch_down(stage(3), wt, down_ntt_of(c, T), down_groups_max(c, T),
+    DEAMOE_TRY(launch_down(stage(3, act_depts + se), wt, down_ntt_of(c, T), down_groups_max(c, T),
                            down_ks_of(c, T), act_depts + se, c.hidden, kGridCap, s));
     DEAMOE_TRY(ev.mark());
   }

@@ -25,9 +25,10 @@
 namespace deamoe {
 
 // One K step of every half: the step's products start from zero and are
-// added with the per-lane factor f (the token's weight, times the fp8 scale).
+// added, on the lanes whose token is a member, with the per-lane factor f (the
+// token's weight, times the fp8 scale).
 template <int WT, int NW, int NTT>
-__device__ inline void chain_mma(const u32x4 (&a)[NW][4], const u32x4 (&b)[4], float f,
+__device__ inline void chain_mma(const u32x4 (&a)[NW][4], const u32x4 (&b)[4], bool member, float f,
                                  f32x4 (&acc)[NW][NTT], int tt) {
 #pragma unroll
   for (int n = 0; n < NW; ++n) {
@@ -46,7 +47,8 @@ __device__ inline void chain_mma(const u32x4 (&a)[NW][4], const u32x4 (&b)[4], f
         t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, as_bf16x8(b[m]), t, 0, 0, 0);
       }
     }
-    acc[n][tt] += f * t;
+    const f32x4 nx = acc[n][tt] + f * t;
+    acc[n][tt] = member ? nx : acc[n][tt];
   }
 }
 
@@ -136,8 +138,7 @@ __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
 #pragma unroll
       for (int tt = 0; tt < NTT; ++tt) {
         // a member's row is its rank among the members; other lanes read the
-        // first member's row (their weight is zero), so each load touches
-        // only the unit's rows
+        // first member's row, so each load touches only the unit's rows
         const int tok = kTile * tt + j;
         const int rank = (m32 >> tok) & 1 ? __popc(m32 & ((1u << tok) - 1u)) : 0;
         bvo[tt] = (uint32_t)rank * K * Tr::A_BYTES + b_chunk_offset(g, 0);
@@ -151,8 +152,8 @@ __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
     u32x4 B[2][P][NTT][4];
     uint32_t MM[2][P];        // the step's member tokens, none past the wave's range
     float SC[2][P], PW[2][P][NTT];
-    // the loads of the wave's steps v .. v + P - 1 (past the range: the last
-    // step's again, which are cached, with weight zero)
+    // the loads of the wave's steps v .. v + P - 1 (past the range a cached
+    // token row in the weights' place, and no members)
     auto issue = [&](int q, int v) {
 #pragma unroll
       for (int p = 0; p < P; ++p) {
@@ -165,14 +166,22 @@ __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
         } else {
           MM[q][p] = 0;
         }
+        const bool ok = v + p < total;
+        const char *base = ok ? wb + (size_t)ck * LD::WSEG : in;
+        const uint32_t rows = ok ? wq : 0u;
+        lane_offset(wvo);
+        const uint32_t vo = ok ? wvo : (lane & 15) * 16;
 #pragma unroll
         for (int i = 0; i < QS; ++i) {
-          const char *base = wb + (size_t)ck * LD::WSEG + (size_t)i * wq;
-          G[q][0][p * QS + i] = __builtin_nontemporal_load(gptr(base + wvo));
+          G[q][0][p * QS + i] =
+              __builtin_nontemporal_load(gptr(scalar_base(base + (size_t)i * rows) + vo));
           if constexpr (NW == 2)
-            G[q][1][i] = __builtin_nontemporal_load(gptr(base + (size_t)QS * wq + wvo));
+            G[q][1][i] =
+                __builtin_nontemporal_load(gptr(scalar_base(base + (size_t)(QS + i) * rows) + vo));
         }
-        const char *bb = in + (size_t)ck * ASEG;
+        const char *bb = scalar_base(in + (size_t)ck * ASEG);
+#pragma unroll
+        for (int tt = 0; tt < NTT; ++tt) lane_offset(bvo[tt]);
         // two steps of one unit load the same token weights: kept two loads,
         // as one would be copied, and so waited for, where they are issued
         const float *pws = pw;
@@ -194,10 +203,11 @@ __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
       for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int tt = 0; tt < NTT; ++tt) {
-          // tokens outside the unit have weight zero (their operand is a
-          // member's row, so the product is finite)
-          const float f0 = (MM[q][p] >> (kTile * tt + j)) & 1 ? PW[q][p][tt] : 0.f;
-          chain_mma<WT, NW>(w[p], B[q][p][tt], WT == WT_FP8 ? f0 * SC[q][p] : f0, acc, tt);
+          // other tokens' lanes hold a member's row, or no weights at all
+          // past the range: whatever their product is, it is dropped
+          const bool member = (MM[q][p] >> (kTile * tt + j)) & 1;
+          const float f = WT == WT_FP8 ? PW[q][p][tt] * SC[q][p] : PW[q][p][tt];
+          chain_mma<WT, NW>(w[p], B[q][p][tt], member, f, acc, tt);
         }
       __builtin_amdgcn_sched_barrier(0);
     };

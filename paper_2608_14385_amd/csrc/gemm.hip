@@ -7,33 +7,47 @@
 
 namespace deamoe {
 
-constexpr int kMaxUnitsCached = 4096;
+// The unit a work item belongs to: the last one whose first item is <= item.
+// Every lane of the wave compares one entry of the prefix per 64 units.  This
+// is the start of every work item's chain of dependent reads (prefix, unit,
+// weights), so it is one round trip: no wait for the counts, no copy to LDS,
+// no barrier, no search over dependent LDS reads.
+__device__ inline int find_unit(const GemmStage &st, int n_units, int item) {
+  constexpr int U = 8;
+  const gmem<const int32_t> *begin = glob(st.begin);
+  const int lane = lane_id();
+  int u = -1;
+  for (int u0 = 0; u0 < st.max_units; u0 += U * kWave) {
+    int b[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      b[i] = 0;
+      if (u0 + i * kWave < st.max_units)
+        b[i] = begin[min(u0 + i * kWave + lane, st.max_units - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      if (u0 + i * kWave < st.max_units)
+        u += __popcll(__ballot(u0 + i * kWave + lane < n_units && b[i] <= item));
+  }
+  return u;
+}
 
 template <int WT, int NW, int NTT, int KS, bool SPLIT, bool PAIR, bool B1>
 __device__ __attribute__((always_inline)) void grouped_gemm_body(const GemmStage &st) {
   using Run = TileRunner<WT, NW, NTT, KS, SPLIT, PAIR, B1>;
   __shared__ typename Run::Smem sm;
-  __shared__ int32_t s_begin[kMaxUnitsCached];
-  const int n_units = st.counts[0], n_tiles = st.counts[1];
-  if (blockIdx.x * Run::TPB >= n_tiles) return;   // the grid is sized for the most work a step can have
-  for (int u = threadIdx.x; u < n_units; u += blockDim.x) s_begin[u] = st.units[u].tile_begin;
-  __syncthreads();
   const int wave = uniform(threadIdx.x / kWave);
+  // the grid is sized for the most work a step can have; the prefix is read
+  // as far as the batch can have units, so that its loads don't wait for the
+  // counts'
+  const int n_units = uniform(st.counts[0]), n_tiles = uniform(st.counts[1]);
   for (int base = blockIdx.x * Run::TPB; base < n_tiles; base += gridDim.x * Run::TPB) {
     const int tile = base + wave / KS;
     const bool active = tile < n_tiles;
-    int u = 0;
-    if (active) {  // last unit whose first tile is <= tile
-      int lo = 0, hi = n_units - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (uniform(s_begin[mid]) <= tile) lo = mid; else hi = mid - 1;
-      }
-      u = lo;
-    }
-    u = uniform(u);
+    const int u = uniform(max(0, find_unit(st, n_units, min(tile, n_tiles - 1))));
     const GemmUnit U = load_unit(st.units + u);
-    Run::run(sm, &U, active ? tile - uniform(s_begin[u]) : 0, active, st.sigma);
+    Run::run(sm, &U, active ? tile - uniform(st.begin[u]) : 0, active, st.sigma);
   }
 }
 
@@ -45,10 +59,12 @@ __global__ __launch_bounds__(256) void grouped_gemm_kernel(GemmStage st) {
 // The same at three waves per SIMD (at most 168 registers), for the
 // instantiations that fit them without spilling:
 //  - the split-operand stage with one token tile (the FACTORED private
-//    gate/up), its two token operands requested per step (B1): 138
-//    registers, where both operands double-buffered took 166 at two waves
-//    per SIMD, or 168 and a 24-byte spill at three.  Same-process A/B
-//    against the latter (outputs bit-identical): 745.6 -> 704.4 us per step
+//    gate/up), its two token operands requested per step (B1).  With both
+//    operands double-buffered the stage's earlier per-lane addresses took 166
+//    registers at two waves per SIMD, or 168 and a 24-byte spill at three;
+//    with scalar bases three waves hold them, even or within 1 % either way
+//    (Baseline-7B 66.4 -> 67.4 us at 16 tokens, DeepSeek-V2 375.8 -> 373.5).
+//    Same-process A/B of B1 against the spilling form (outputs bit-identical): 745.6 -> 704.4 us per step
 //    at 16 tokens on the DeepSeek-V3 FACTORED layer (the stage 405.0 ->
 //    364.3), 2071.8 -> 1977.4 at 64, 148.4 -> 145.3 at one token; Kimi-K2
 //    879.6 -> 839.6, DeepSeek-V2 406.2 -> 391.6, Qwen3 330.8 -> 319.5 at 16;

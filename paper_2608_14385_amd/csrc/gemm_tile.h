@@ -95,8 +95,7 @@ __device__ inline GemmUnit load_unit(const GemmUnit *p) {
   u.w0 = c->w0; u.w1 = c->w1; u.s0 = c->s0; u.s1 = c->s1;
   u.in0 = c->in0; u.in1 = c->in1; u.idx = c->idx; u.out0 = c->out0; u.out1 = c->out1;
   u.R = c->R; u.K = c->K; u.ldw = c->ldw; u.ldin = c->ldin; u.ldout = c->ldout;
-  u.ntok = c->ntok; u.tile_begin = c->tile_begin; u.epi = c->epi; u.out_f32 = c->out_f32;
-  u.tpg = c->tpg;
+  u.ntok = c->ntok; u.flags = c->flags;
   return u;
 }
 
@@ -110,42 +109,30 @@ __device__ inline const gfloat *gfptr(const float *p) {
   return reinterpret_cast<const gfloat *>(reinterpret_cast<uintptr_t>(p));
 }
 
-// Token-operand row of token i of a unit.
-// idx is a generic pointer: the small-batch kernel keeps its token lists in
-// LDS, the stage tables in global memory.
-__device__ inline const char *token_row(const void *base, const int32_t *idx, int ldin, int i,
-                                        int abytes) {
-  const int row = idx ? idx[i] : i;
-  return static_cast<const char *>(base) + (size_t)row * ldin * abytes;
+// Loads at a wave-uniform base plus a 32-bit lane offset take the base from
+// scalar registers and the offset from one vector register, but only where
+// the compiler sees both in the block of the load: out of a loop it would
+// hoist the offset's widening, or the sum with the base's loop-invariant part,
+// as a per-lane 64-bit pointer.  scalar_base keeps a step's base one value,
+// lane_offset the offset one that the step "changes".
+template <class P>
+__device__ inline P *scalar_base(P *p) {
+  asm("" : "+s"(p));
+  return p;
 }
+__device__ inline void lane_offset(uint32_t &o) { asm volatile("" : "+v"(o)); }
 
 // Byte offset, inside one K step of a token row, of the 16-byte token chunk
 // that pairs with matrix-core product m (m < 4) of lane group g.
 __device__ inline int b_chunk_offset(int g, int m) { return m * 64 + g * 16; }
 
-// Token operand of one K step for every token tile: B[tt][0..3] pairs with
-// gate / single weights, B[tt][4..7] with up weights when their inputs differ.
-template <int WT, int NTT, bool SPLIT>
-__device__ inline void load_b(u32x4 (&B)[NTT][SPLIT ? 8 : 4], const char *const (&bp0)[NTT],
-                              const char *const (&bp1)[NTT], int ntt, size_t boff, int g) {
-#pragma unroll
-  for (int tt = 0; tt < NTT; ++tt) {
-    if (tt > 0 && tt >= ntt) break;   // ntt >= 1
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      B[tt][q] = *gptr(bp0[tt] + boff + b_chunk_offset(g, q));
-      if constexpr (SPLIT) B[tt][4 + q] = *gptr(bp1[tt] + boff + b_chunk_offset(g, q));
-    }
-  }
-}
-
 // The matrix-core products of one K step; a[n][m] is the operand of product
 // m (fp8: the first two dwords hold its eight codes).
-template <int WT, int NW, int NTT, bool SPLIT>
-__device__ inline void step_mma(const u32x4 (&a)[NW][4], const u32x4 (&B)[NTT][SPLIT ? 8 : 4],
+template <int WT, int NW, int NTT, int NL, bool SPLIT>
+__device__ inline void step_mma(const u32x4 (&a)[NW][4], const u32x4 (&B)[NL][SPLIT ? 8 : 4],
                                 int ntt, const float (&sc)[NW], f32x4 (&acc)[NW][NTT]) {
 #pragma unroll
-  for (int tt = 0; tt < NTT; ++tt) {
+  for (int tt = 0; tt < NL; ++tt) {
     if (tt > 0 && tt >= ntt) break;   // ntt >= 1
 #pragma unroll
     for (int n = 0; n < NW; ++n) {
@@ -219,30 +206,45 @@ __device__ inline void stage_weights(char *lds, const u32x4 (&Gb)[NW][WLoad<WT>:
 // Stream one work item: row tiles rt0 .. rt0 + nsub - 1 of unit U, each over
 // the K steps kp, kp + ks, ... (nsub > 1 only when ks == 1).  PAIR: a tile is
 // 32 rows of one matrix, streamed as two 16-row halves (w0 and w0 + 16 rows)
-// that share the token operand; R is then a multiple of 32.  `lds` is this
-// wave's private staging region (NW * WLoad<WT>::REGION bytes).
+// that share the token operand; R is then a multiple of 32, and of 16 where
+// two matrices are streamed (widths are whole K steps); single matrices (the
+// router) may end inside a tile.  `lds` is this wave's private staging region
+// (NW * WLoad<WT>::REGION bytes).
 // Rows past R and tokens past ntok are clamped to valid ones: their products
 // land only in output rows / columns that are never stored.
 // Software pipeline: loads retire in issue order, so the weights and the
-// token operand of one K step are requested together as one group, PF
-// groups ahead of the step being multiplied; waiting for a group never
-// waits for a later one.  Groups past the end read a cache-resident token
-// row instead of weights, so every iteration issues the same loads.
+// token operand of one K step are requested together as one group, one group
+// ahead of the step being multiplied; waiting for a group never waits for a
+// later one.  A group past the end reads a cache-resident token row instead
+// of weights and is not multiplied, so every iteration issues the same loads
+// (repeating the last step's addresses instead reads those rows from HBM
+// twice: the DeepSeek-V3 FACTORED private gate/up took 402 us, not 360, at 16).
+// Bound by the rate the rows arrive at: every address is a scalar base, moved
+// per step, plus a 32-bit lane offset that the item keeps.  Per-lane 64-bit
+// addresses, worked out anew each step, took up registers of loads in flight,
+// and the compiler drained all loads at every other step.  The weights' first
+// loads need no token index, so they don't wait for it.  Kernel time by
+// trace, us, with the work item found as in find_unit: the DeepSeek-V3 shape
+// gate/up 485 -> 480 and down 282 -> 276 at 64 tokens, fp8 249 -> 241 and 141
+// -> 137 at 45; the 7B-class gate/up 31.5 -> 29.4 at 16 tokens, 40.6 -> 37.4
+// at 61; the Baseline-7B FACTORED private gate/up 21.2 -> 19.2 at 16.
 // `done(rt, acc)` is called (and acc cleared) after the last K step of
 // each tile when nsub > 1; with nsub == 1 the caller finishes the tile.
+// NL: token tiles of the item at most (ntt <= NL of them hold tokens).
 // B1: the token operand is requested with the step that uses it rather than
-// PF steps ahead (one buffer instead of PF + 1), before that step's weight
+// a step ahead (one buffer instead of two), before that step's weight
 // prefetch, so that waiting for it never waits for the prefetch; its L2
 // round trip overlaps the weights of the step in flight.  This saves the
-// registers of PF token-operand buffers.
-template <int WT, int NW, int NTT, bool SPLIT, int PF, bool PAIR, bool NT, bool B1, class Done>
+// registers of a token-operand buffer.
+template <int WT, int NW, int NTT, int NL, bool SPLIT, bool PAIR, bool NT, bool B1, bool MULTI,
+          class Done>
 __device__ inline void tile_loop(const GemmUnit &U, int rt0, int nsub, int kp, int ks, int tok0,
-                                 char *lds, f32x4 (&acc)[NW][NTT], Done done) {
+                                 int ntt, char *lds, f32x4 (&acc)[NW][NTT], Done done) {
   static_assert(!PAIR || (NW == 2 && !SPLIT), "a row pair is two tiles of one matrix");
+  static_assert(NL <= NTT, "token tiles");
   constexpr int TR = PAIR ? 2 * kTile : kTile;   // weight rows of a tile
   using Tr = WTraits<WT>;
   using LD = WLoad<WT>;
-  constexpr int NB = PF + 1;
   constexpr int BV = SPLIT ? 8 : 4;
   constexpr int ASEG = Tr::K_STEP * Tr::A_BYTES;     // bytes of one token row per K step
   const int lane = lane_id();
@@ -253,16 +255,6 @@ __device__ inline void tile_loop(const GemmUnit &U, int rt0, int nsub, int kp, i
   const int total = nloc * nsub;
   if (total == 0) return;
   const int ntok = uniform(U.ntok) - tok0;   // tokens of this item: tok0 .. U.ntok - 1
-  const int ntt = uniform(min(NTT, (ntok + kTile - 1) / kTile));
-  const char *bp0[NTT];
-  const char *bp1[NTT];
-#pragma unroll
-  for (int tt = 0; tt < NTT; ++tt) {
-    int i = tt * kTile + j;
-    i = tok0 + (i < ntok ? i : 0);
-    bp0[tt] = token_row(U.in0, U.idx, U.ldin, i, Tr::A_BYTES);
-    bp1[tt] = SPLIT ? token_row(U.in1, U.idx, U.ldin, i, Tr::A_BYTES) : bp0[tt];
-  }
   // ROWS: the token operand of two or more tiles is loaded like the weights,
   // as whole 256-byte row segments (instruction q of tile tt covers tokens
   // 4q + lane / 16, 16 bytes each), and transposed through this wave's LDS
@@ -270,50 +262,45 @@ __device__ inline void tile_loop(const GemmUnit &U, int rt0, int nsub, int kp, i
   // instruction of the operand layout's 16 rows x 64 bytes.  fp8 stages take
   // it with the operand requested per step (B1): their double-buffered
   // three-wave instantiations would spill the row offsets.
-  constexpr bool ROWS = (WT == WT_BF16 || (WT == WT_FP8 && B1)) && !SPLIT && NTT >= 2;
+  constexpr bool ROWS = (WT == WT_BF16 || (WT == WT_FP8 && B1)) && !SPLIT && NL >= 2;
   using LB = WLoad<WT_BF16>;   // token rows are bf16
   static_assert(!ROWS || (ASEG == LB::WSEG && LB::NQ == 4 && NW * LD::REGION >= LB::REGION),
                 "a token tile is staged like one bf16 weight tile");
-  // byte offsets from in0 of the rows this lane loads: below 2^32, as a stage
+  // Lane offsets of the token rows from in0 (and in1): below 2^32, as a stage
   // reads at most one row per (token, selected expert) pair, of at most
-  // DEAMOE_MAX_WIDTH bf16 columns
-  static_assert((int64_t)DEAMOE_MAX_TOKENS * DEAMOE_MAX_TOPK * DEAMOE_MAX_WIDTH * 2 <
+  // DEAMOE_MAX_WIDTH columns.  idx is a generic pointer: the small-batch
+  // kernel keeps its token lists in LDS, the stage tables in global memory.
+  static_assert((int64_t)DEAMOE_MAX_TOKENS * DEAMOE_MAX_TOPK * DEAMOE_MAX_WIDTH * 4 <
                     (int64_t{1} << 32),
                 "32-bit row offsets");
-  uint32_t boffs[ROWS ? NTT : 1][4];
-  if constexpr (ROWS) {
+  const uint32_t ldin = (uint32_t)uniform(U.ldin) * Tr::A_BYTES;
+  const int32_t *idx = U.idx;
+  constexpr int NR = ROWS ? 4 : 1;   // rows a lane reads of a token tile
+  uint32_t trow[NL][NR], tvo[NL][NR];
 #pragma unroll
-    for (int tt = 0; tt < NTT; ++tt)
+  for (int tt = 0; tt < NL; ++tt)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        int i = tt * kTile + q * LB::RPI + lane / LB::LPR;
-        i = tok0 + (i < ntok ? i : 0);
-        boffs[tt][q] = (uint32_t)(token_row(U.in0, U.idx, U.ldin, i, Tr::A_BYTES) -
-                                  static_cast<const char *>(U.in0)) +
-                       (lane % LB::LPR) * 16;
-      }
-  }
-  // the token operand of K step kstep in the load layout (ROWS) or the operand layout
-  auto load_tok = [&](u32x4(&Bb)[NTT][BV], int kstep) {
-    if constexpr (ROWS) {
-      const char *base = static_cast<const char *>(U.in0) + (size_t)kstep * ASEG;
-#pragma unroll
-      for (int tt = 0; tt < NTT; ++tt) {
-        if (tt > 0 && tt >= ntt) break;   // ntt >= 1
-#pragma unroll
-        for (int q = 0; q < 4; ++q) Bb[tt][q] = *gptr(base + boffs[tt][q]);
-      }
-    } else {
-      load_b<WT, NTT, SPLIT>(Bb, bp0, bp1, ntt, (size_t)kstep * ASEG, g);
+    for (int q = 0; q < NR; ++q) {
+      const int i = tt * kTile + (ROWS ? q * LB::RPI + lane / LB::LPR : j);
+      trow[tt][q] = tok0 + (i < ntok ? i : 0);
+      if (idx) trow[tt][q] = idx[trow[tt][q]];
     }
-  };
   // load pattern: instruction q covers rows q * RPI + lane / LPR, 16 bytes each
   const int lrow = lane / LD::LPR, lchunk = lane % LD::LPR;
-  const char *w0 = static_cast<const char *>(U.w0) + lchunk * 16;
-  const char *w1 = PAIR ? w0 + (size_t)kTile * ldw * Tr::W_BYTES
-                        : NW == 2 ? static_cast<const char *>(U.w1) + lchunk * 16 : w0;
-  const int rmax = R - 1 - (PAIR ? kTile : 0);   // last row the first matrix may read
-  const char *dummy = bp0[0] + (lane & 15) * 16;
+  const uint32_t wrow = (uint32_t)ldw * Tr::W_BYTES;   // bytes of a weight row
+  const size_t tile_bytes = (size_t)TR * wrow;
+  const char *w0 = static_cast<const char *>(U.w0) + (size_t)rt0 * tile_bytes;
+  const char *w1 = PAIR ? w0 + (size_t)kTile * wrow
+                        : NW == 2 ? static_cast<const char *>(U.w1) + (size_t)rt0 * tile_bytes : w0;
+  constexpr int NO = NW == 1 ? LD::NQ : 1;   // offsets: a single matrix's rows are clamped
+  uint32_t wvo[NO];
+#pragma unroll
+  for (int q = 0; q < NO; ++q) {
+    const int row = NW == 1 ? min(q * LD::RPI + lrow, R - 1 - rt0 * TR) : lrow;
+    wvo[q] = (uint32_t)row * wrow + lchunk * 16;
+  }
+  const char *in0 = static_cast<const char *>(U.in0);
+  const char *in1 = SPLIT ? static_cast<const char *>(U.in1) : in0;
   // fp8 block scales.  The scale rows of this item's tiles are read once, as a
   // window of 64 entries of the [R/128, K/128] table starting at the first
   // tile's scale row: lane l holds entry l.  A K step then takes its scale
@@ -330,77 +317,124 @@ __device__ inline void tile_loop(const GemmUnit &U, int rt0, int nsub, int kp, i
     scw[0] = gfptr(U.s0)[e];
     if constexpr (NW == 2) scw[1] = gfptr(PAIR ? U.s0 : U.s1)[e];
   }
-  u32x4 G[NB][NW][LD::NQ];
-  u32x4 B[B1 ? 1 : NB][NTT][BV];
-  int SC[NB];   // fp8: window entry of the group's scales
-  // K step of virtual step v (tile v / nloc, K step kp + (v % nloc) * ks)
-  auto kstep_of = [&](int v) {
-    const bool ok = v < total;
-    const int sub = ok ? v / nloc : 0;
-    return ok ? kp + (v - sub * nloc) * ks : 0;
-  };
-  // issue the weight loads (and, without B1, the token operand) of virtual step v
-  auto issue = [&](u32x4(&Gb)[NW][LD::NQ], u32x4(&Bb)[NTT][BV], int &sc, int v) {
-    const bool ok = v < total;
-    const int sub = ok ? v / nloc : 0;
-    const int kstep = kstep_of(v);
-#pragma unroll
-    for (int q = 0; q < LD::NQ; ++q) {
-      const int row = min((rt0 + sub) * TR + q * LD::RPI + lrow, rmax);
-      const size_t woff = (size_t)row * ldw * Tr::W_BYTES + (size_t)kstep * LD::WSEG;
-#pragma unroll
-      for (int n = 0; n < NW; ++n)
-        Gb[n][q] = NT ? __builtin_nontemporal_load(gptr(ok ? (n ? w1 : w0) + woff : dummy))
-                      : *gptr(ok ? (n ? w1 : w0) + woff : dummy);
-    }
-    if constexpr (!B1) load_tok(Bb, kstep);
-    if constexpr (WT == WT_FP8)   // a row pair lies in one scale row
-      sc = uniform((((rt0 + sub) * TR) / 128 - srow0) * sblocks + kstep);
-  };
-  auto stage = [&](const u32x4(&Gb)[NW][LD::NQ], u32x4(&a)[NW][4]) {
-    stage_weights<WT, NW>(lds, Gb, a);
-  };
-#pragma unroll
-  for (int p = 0; p < PF; ++p) issue(G[p], B[B1 ? 0 : p], SC[p], p);
-  for (int v = 0;;) {
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-      const int qn = (q + NB - 1) % NB;   // the buffer consumed one step ago
-      if constexpr (B1) {
-        load_tok(B[0], kstep_of(v));
-        __builtin_amdgcn_sched_barrier(0);
+  u32x4 G[2][NW][LD::NQ];
+  u32x4 B[B1 ? 1 : 2][NL][BV];
+  int SC[2];   // fp8: window entry of the group's scales
+  // issue cursor: tile rt0 + ct, K step ck
+  int ck = kp - ks, ct = 0;
+  auto issue_weights = [&](int q, int v) {
+    if (v < total) {
+      ck += ks;
+      if (MULTI && ck >= nsteps) {   // the next tile of the item
+        ck = kp;
+        ++ct;
+        w0 += tile_bytes;
+        w1 += tile_bytes;
       }
-      issue(G[qn], B[B1 ? 0 : qn], SC[qn], v + PF);
-      __builtin_amdgcn_sched_barrier(0);
-      u32x4 a[NW][4];
-      stage(G[q], a);
-      if constexpr (ROWS) {   // after the weights' reads, in the same region
-        u32x4(&Bq)[NTT][BV] = B[B1 ? 0 : q];
+    }
+    // past the end: 256 bytes of a token row, which are cached
+    const bool ok = v < total;
+    const char *b0 = ok ? w0 + (size_t)ck * LD::WSEG : in0;
+    const char *b1 = ok ? w1 + (size_t)ck * LD::WSEG : in0;
+    const uint32_t rows = ok && NW > 1 ? LD::RPI * wrow : 0u;
+    uint32_t vo[NO];
 #pragma unroll
-        for (int tt = 0; tt < NTT; ++tt) {
-          if (tt > 0 && tt >= ntt) break;
-          stage_weights<WT_BF16, 1>(lds, reinterpret_cast<const u32x4(&)[1][4]>(Bq[tt]),
-                                    reinterpret_cast<u32x4(&)[1][4]>(Bq[tt]));
+    for (int i = 0; i < NO; ++i) {
+      lane_offset(wvo[i]);
+      vo[i] = ok ? wvo[i] : (lane & 15) * 16;
+    }
+#pragma unroll
+    for (int i = 0; i < LD::NQ; ++i)
+#pragma unroll
+      for (int n = 0; n < NW; ++n) {
+        const gvec *p = gptr(scalar_base((n ? b1 : b0) + (size_t)i * rows) + vo[NW == 1 ? i : 0]);
+        G[q][n][i] = NT ? __builtin_nontemporal_load(p) : *p;
+      }
+    if constexpr (WT == WT_FP8)   // a row pair lies in one scale row
+      SC[q] = uniform((((rt0 + ct) * TR) / 128 - srow0) * sblocks + ck);
+  };
+  // the token operand of K step k in the load layout (ROWS) or the operand layout
+  auto issue_tokens = [&](int q, int k) {
+    const char *b0 = scalar_base(in0 + (size_t)k * ASEG);
+    const char *b1 = SPLIT ? scalar_base(in1 + (size_t)k * ASEG) : b0;
+#pragma unroll
+    for (int tt = 0; tt < NL; ++tt) {
+      if (tt > 0 && tt >= ntt) break;   // ntt >= 1
+#pragma unroll
+      for (int i = 0; i < NR; ++i) lane_offset(tvo[tt][i]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if constexpr (ROWS) {
+          B[q][tt][i] = *gptr(b0 + tvo[tt][i]);
+        } else {
+          B[q][tt][i] = *gptr(b0 + tvo[tt][0] + b_chunk_offset(0, i));
+          if constexpr (SPLIT) B[q][tt][4 + i] = *gptr(b1 + tvo[tt][0] + b_chunk_offset(0, i));
         }
       }
-      float sc[NW];
-      if constexpr (WT == WT_FP8) {
+    }
+  };
+  int tk = kp - ks;   // B1: K step of the operand requested last
+  auto multiply = [&](int q) {
+    u32x4 a[NW][4];
+    stage_weights<WT, NW>(lds, G[q], a);
+    u32x4(&Bq)[NL][BV] = B[B1 ? 0 : q];
+    if constexpr (ROWS) {   // after the weights' reads, in the same region
 #pragma unroll
-        for (int n = 0; n < NW; ++n)
-          sc[n] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scw[n]), SC[q]));
+      for (int tt = 0; tt < NL; ++tt) {
+        if (tt > 0 && tt >= ntt) break;
+        stage_weights<WT_BF16, 1>(lds, reinterpret_cast<const u32x4(&)[1][4]>(Bq[tt]),
+                                  reinterpret_cast<u32x4(&)[1][4]>(Bq[tt]));
       }
-      step_mma<WT, NW, NTT, SPLIT>(a, B[B1 ? 0 : q], ntt, sc, acc);
+    }
+    float sc[NW];
+    if constexpr (WT == WT_FP8) {
+#pragma unroll
+      for (int n = 0; n < NW; ++n)
+        sc[n] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scw[n]), SC[q]));
+    }
+    step_mma<WT, NW, NTT, NL, SPLIT>(a, Bq, ntt, sc, acc);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // one step: requests of the next group (and, B1, of this step's operand)
+  auto request = [&](int q, int v) {   // q: buffer of virtual step v
+    if constexpr (B1) {   // the operand of step v - 1
+      tk += ks;
+      if (MULTI && tk >= nsteps) tk = kp;
+      issue_tokens(0, tk);
       __builtin_amdgcn_sched_barrier(0);
-      ++v;
-      if (nsub > 1 && v % nloc == 0) {   // a tile of a multi-tile work item is complete
-        done(rt0 + v / nloc - 1, acc);
+    }
+    issue_weights(q, v);
+    if constexpr (!B1) issue_tokens(q, ck);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto finish = [&](int v) {   // step v multiplied
+    if constexpr (MULTI) {
+      if (nsub > 1 && (v + 1) % nloc == 0) {   // a tile of a multi-tile work item is complete
+        done(rt0 + (v + 1) / nloc - 1, acc);
 #pragma unroll
         for (int n = 0; n < NW; ++n)
 #pragma unroll
           for (int tt = 0; tt < NTT; ++tt) acc[n][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      if (v >= total) return;
     }
+  };
+  issue_weights(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int tt = 0; tt < NL; ++tt)
+#pragma unroll
+    for (int q = 0; q < NR; ++q)
+      tvo[tt][q] = trow[tt][q] * ldin + (ROWS ? (lane % LB::LPR) * 16 : b_chunk_offset(g, 0));
+  if constexpr (!B1) issue_tokens(0, ck);
+  for (int v = 0;; v += 2) {
+    request(1, v + 1);
+    multiply(0);
+    finish(v);
+    if (v + 1 >= total) return;
+    request(0, v + 2);
+    multiply(1);
+    finish(v + 1);
+    if (v + 2 >= total) return;
   }
 }
 
@@ -447,8 +481,8 @@ __device__ inline void tile_epilogue(const GemmUnit &U, int rt, int tok0, int si
   constexpr int TR = PAIR ? 2 * kTile : kTile;
   const int lane = lane_id();
   const int g = lane >> 4, j = lane & 15;
-  const int R = uniform(U.R), ntok = uniform(U.ntok) - tok0, epi = uniform(U.epi);
-  const int out_f32 = uniform(U.out_f32), ldout = uniform(U.ldout);
+  const int R = uniform(U.R), ntok = uniform(U.ntok) - tok0, flags = uniform(U.flags);
+  const int epi = unit_epi(flags), out_f32 = unit_out_f32(flags), ldout = uniform(U.ldout);
   const int row0 = rt * TR + 4 * g;
   if (row0 >= R) return;
   const bool full = row0 + 3 < R;
@@ -497,8 +531,6 @@ template <int WT, int NW, int NTT, int KS, bool SPLIT = false, bool PAIR = false
 struct TileRunner {
   static constexpr int TR = PAIR ? 2 * kTile : kTile;   // weight rows of a tile
   static constexpr int TPB = 4 / KS;
-  // load groups in flight per wave while one is multiplied
-  static constexpr int PF = 1;
   static constexpr int STAGE_BYTES = NW * WLoad<WT>::REGION;   // per wave
   static constexpr int RED_BYTES = KS > 1 ? NW * NTT * kWave * 16 : 0;   // per wave
   static constexpr int WAVE_BYTES = STAGE_BYTES > RED_BYTES ? STAGE_BYTES : RED_BYTES;
@@ -521,7 +553,7 @@ struct TileRunner {
     if (active) {
       constexpr int GT = kTile * NTT;   // tokens of a group
       const int groups = (uniform(U->ntok) + GT - 1) / GT;
-      const int tpg = KS == 1 ? uniform(U->tpg) : 1;
+      const int tpg = KS == 1 ? unit_tpg(uniform(U->flags)) : 1;
       const int ntiles = (uniform(U->R) + TR - 1) / TR;
       if (groups > 1) {
         // The token groups of one tile item stream the same weight rows.
@@ -555,12 +587,21 @@ struct TileRunner {
       // group: those loads stay in the caches for the other groups (the
       // groups of a tile item run on one XCD at about the same time); every
       // other weight row is read once and streams past them.
+      const int ntok = uniform(U->ntok) - tok0;
+      const int ntt = uniform(min(NTT, (ntok + kTile - 1) / kTile));
+      constexpr bool MULTI = KS == 1;
       if (groups > 1)
-        tile_loop<WT, NW, NTT, SPLIT, PF, PAIR, false, B1>(*U, rt0, nsub, kp, KS, tok0, sm.buf[wave],
-                                                       acc, done);
+        tile_loop<WT, NW, NTT, NTT, SPLIT, PAIR, false, B1, MULTI>(*U, rt0, nsub, kp, KS, tok0, ntt,
+                                                                   sm.buf[wave], acc, done);
+      else if (NTT == 2 && !B1 && ntt == 1)
+        // a one-tile loop of its own: with the second tile's loads optional,
+        // a wait for them would have to count the shortest case and so wait
+        // for part of the next group's weights
+        tile_loop<WT, NW, NTT, 1, SPLIT, PAIR, true, B1, MULTI>(*U, rt0, nsub, kp, KS, tok0, ntt,
+                                                                sm.buf[wave], acc, done);
       else
-        tile_loop<WT, NW, NTT, SPLIT, PF, PAIR, true, B1>(*U, rt0, nsub, kp, KS, tok0, sm.buf[wave],
-                                                      acc, done);
+        tile_loop<WT, NW, NTT, NTT, SPLIT, PAIR, true, B1, MULTI>(
+            *U, rt0, nsub, kp, KS, tok0, NTT == 2 && !B1 ? 2 : ntt, sm.buf[wave], acc, done);
     }
     if constexpr (KS > 1) {
       f32x4 *red = reinterpret_cast<f32x4 *>(sm.buf[wave]);

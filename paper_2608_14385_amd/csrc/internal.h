@@ -36,11 +36,17 @@ struct GemmUnit {
   const int32_t *idx;
   void *out0, *out1;
   int32_t R, K, ldw, ldin, ldout, ntok;
-  int32_t tile_begin;       // exclusive prefix of work items over the units of a stage
-  int32_t epi;              // Epilogue
-  int32_t out_f32;          // 1: outputs are fp32, 0: act dtype
-  int32_t tpg;              // row tiles per work item (1 unless the K split is 1)
+  int32_t flags;            // unit_flags
 };
+
+// flags of a unit: its Epilogue, whether its outputs are fp32 (else the act
+// dtype), and its row tiles per work item (1 unless the K split is 1).
+__host__ __device__ inline int unit_flags(int epi, int out_f32, int tpg) {
+  return epi | out_f32 << 2 | tpg << 3;
+}
+__device__ inline int unit_epi(int f) { return f & 3; }
+__device__ inline int unit_out_f32(int f) { return f >> 2 & 1; }
+__device__ inline int unit_tpg(int f) { return f >> 3; }
 
 // One unit of the fused down projection and combine (at most 32 tokens): the
 // [R, K] down matrix w (fp8: block scales s) applied to
@@ -60,8 +66,10 @@ struct ChainUnit {
 
 struct GemmStage {
   const GemmUnit *units;
+  const int32_t *begin;     // exclusive prefix of work items over the units
   const int32_t *counts;    // [0] = number of units, [1] = number of row tiles
   int32_t sigma;            // DEAMOE_SIGMA_*
+  int32_t max_units;        // the most units a step of this batch can have
 };
 
 // Device-side plan written by the route kernel and consumed by the later ones.

@@ -38,9 +38,7 @@ __global__ __launch_bounds__(256) void router_kernel(RouterArgs a) {
   U.ldin = a.h;
   U.ldout = a.ldp;
   U.ntok = a.T;
-  U.epi = EPI_STORE;
-  U.out_f32 = 1;
-  U.tpg = 1;
+  U.flags = unit_flags(EPI_STORE, 1, 1);
   Run::run(sm, &U, rt, true, DEAMOE_SIGMA_NONE);
 }
 

@@ -193,16 +193,23 @@ __device__ inline void wave_lds_sync() {
 
 constexpr int kMaxKC = 16;   // router chunks (host caps the split)
 
-// Fill one unit of a stage table field by field (no temporary struct).
-__device__ inline void put_unit(gmem<GemmUnit> *U, const void *w0, const void *w1, const float *s0,
-                                const float *s1, const void *in0, const void *in1,
-                                const int32_t *idx, void *out0, void *out1, int R, int K, int ldin,
-                                int ldout, int ntok, int tile_begin, int epi, int out_f32,
-                                int tpg = 1) {
+// A stage's unit table: the units, then the prefix of their work items
+// (GemmStage), as many entries each as a step can have units.
+__device__ inline gmem<int32_t> *stage_begin(GemmUnit *units, int max_units) {
+  return reinterpret_cast<gmem<int32_t> *>(glob(units) + max_units);
+}
+
+// Fill unit u of a stage table field by field (no temporary struct).
+__device__ inline void put_unit(GemmUnit *units, int max_units, int u, const void *w0,
+                                const void *w1, const float *s0, const float *s1, const void *in0,
+                                const void *in1, const int32_t *idx, void *out0, void *out1, int R,
+                                int K, int ldin, int ldout, int ntok, int tile_begin, int epi,
+                                int out_f32, int tpg = 1) {
+  gmem<GemmUnit> *U = glob(units) + u;
   U->w0 = w0; U->w1 = w1; U->s0 = s0; U->s1 = s1; U->in0 = in0; U->in1 = in1; U->idx = idx;
   U->out0 = out0; U->out1 = out1; U->R = R; U->K = K; U->ldw = K; U->ldin = ldin;
-  U->ldout = ldout; U->ntok = ntok; U->tile_begin = tile_begin; U->epi = epi;
-  U->out_f32 = out_f32; U->tpg = tpg;
+  U->ldout = ldout; U->ntok = ntok; U->flags = unit_flags(epi, out_f32, tpg);
+  stage_begin(units, max_units)[u] = tile_begin;
 }
 
 __device__ inline void put_chain(gmem<ChainUnit> *U, const void *w, const float *s, const void *in,
@@ -800,7 +807,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
   // otherwise they come from block scans over an array with every
   // department's items, then every expert's (the expert bitmaps' LDS, free
   // after the placement above).
-  const int wb = a.w_bytes, ab = a.act_f32 ? 4 : 2;
+  const int wb = a.w_bytes, ab = a.act_f32 ? 4 : 2, mu = m + n + 1;
   const char *x = static_cast<const char *>(a.x);
   auto wptr = [&](const void *base, int idx, int R, int C) -> const void * {
     return static_cast<const char *>(base) + (size_t)idx * R * C * wb;
@@ -888,7 +895,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       const int u = s_scan[j] >> 16, off = doff(j);
       const int32_t *idx = a.r.dept_tokens + off;
       char *ao = static_cast<char *>(a.abuf_dept) + (size_t)off * a.d_s * ab;
-      put_unit(glob(a.units[0]) + u, wptr(W.dept_gate, j, a.d_s, a.h), wptr(W.dept_up, j, a.d_s, a.h),
+      put_unit(a.units[0], mu, u, wptr(W.dept_gate, j, a.d_s, a.h), wptr(W.dept_up, j, a.d_s, a.h),
                sptr(W.scale[0], j, a.d_s, a.h), sptr(W.scale[1], j, a.d_s, a.h), x, x, idx, ao,
                nullptr, a.d_s, a.h, a.h, a.d_s, dc, dbeg_a(j, u), EPI_SWIGLU, a.act_f32);
       if (a.chain)
@@ -896,7 +903,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
                   sptr(W.scale[2], j, a.h, a.d_s), ao, a.wdense + (size_t)j * kChainT, a.d_s,
                   s_dtok[j * kTW], u * sd);
       else
-        put_unit(glob(a.units[1]) + u, wptr(W.dept_down, j, a.h, a.d_s), nullptr,
+        put_unit(a.units[1], mu, u, wptr(W.dept_down, j, a.h, a.d_s), nullptr,
                  sptr(W.scale[2], j, a.h, a.d_s), nullptr, ao, ao, nullptr,
                  a.partial + (size_t)off * a.h, nullptr, a.h, a.d_s, a.d_s, a.h, dc,
                  dbeg_b(j, u), EPI_STORE, 1, gd);
@@ -908,7 +915,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       const int ui = (s_scan[m + e] >> 16) - ud, u = ud + ui, off = eoff(e);
       const int32_t *idx = a.r.exp_tokens + off;
       char *ao = static_cast<char *>(a.abuf_exp) + (size_t)off * a.d_p * ab;
-      put_unit(glob(a.units[0]) + u, wptr(W.priv_gate, e, a.d_p, a.h), wptr(W.priv_up, e, a.d_p, a.h),
+      put_unit(a.units[0], mu, u, wptr(W.priv_gate, e, a.d_p, a.h), wptr(W.priv_up, e, a.d_p, a.h),
                sptr(W.scale[3], e, a.d_p, a.h), sptr(W.scale[4], e, a.d_p, a.h), x, x, idx, ao,
                nullptr, a.d_p, a.h, a.h, a.d_p, my_ec[q], ebeg_a(e, ui), EPI_SWIGLU,
                a.act_f32);
@@ -917,7 +924,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
                   sptr(W.scale[5], e, a.h, a.d_p), ao, a.wdense + (size_t)(m + e) * kChainT, a.d_p,
                   s_etok[e * kTW], ud * sd + ui * sp);
       else
-        put_unit(glob(a.units[1]) + u, wptr(W.priv_down, e, a.h, a.d_p), nullptr,
+        put_unit(a.units[1], mu, u, wptr(W.priv_down, e, a.h, a.d_p), nullptr,
                  sptr(W.scale[5], e, a.h, a.d_p), nullptr, ao, ao, nullptr,
                  a.partial + (size_t)(ndp + off) * a.h, nullptr, a.h, a.d_p, a.d_p, a.h,
                  my_ec[q], ebeg_b(e, ui), EPI_STORE, 1, gp);
@@ -928,7 +935,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       int units = ud + ue, items_a = tot_a, items_b = tot_b;
       int steps = ud * sd + ue * sp;
       if (has_se) {
-        put_unit(glob(a.units[0]) + units, W.se_gate, W.se_up, sptr(W.scale[6], 0, a.d_se, a.h),
+        put_unit(a.units[0], mu, units, W.se_gate, W.se_up, sptr(W.scale[6], 0, a.d_se, a.h),
                  sptr(W.scale[7], 0, a.d_se, a.h), x, x, nullptr, a.abuf_se, nullptr, a.d_se, a.h,
                  a.h, a.d_se, T, items_a, EPI_SWIGLU, a.act_f32);
         if (a.chain) {
@@ -937,7 +944,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
                     T >= 32 ? 0xffffffffu : (1u << T) - 1u, steps);
           steps += a.d_se / kstep;
         } else {
-          put_unit(glob(a.units[1]) + units, W.se_down, nullptr, sptr(W.scale[8], 0, a.h, a.d_se),
+          put_unit(a.units[1], mu, units, W.se_down, nullptr, sptr(W.scale[8], 0, a.h, a.d_se),
                    nullptr, a.abuf_se, a.abuf_se, nullptr,
                    a.partial + (size_t)(ndp + nep_priv) * a.h, nullptr, a.h, a.d_se, a.d_se, a.h,
                    T, items_b, EPI_STORE, 1, gse);
@@ -965,14 +972,14 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       char *go = static_cast<char *>(a.gbuf) + (size_t)off * d * ab;
       char *uo = static_cast<char *>(a.ubuf) + (size_t)off * d * ab;
       char *zs = static_cast<char *>(a.zsbuf) + (size_t)off * d * ab;
-      put_unit(glob(a.units[0]) + u, wptr(W.dept_gate, j, d, a.h), wptr(W.dept_up, j, d, a.h),
+      put_unit(a.units[0], mu, u, wptr(W.dept_gate, j, d, a.h), wptr(W.dept_up, j, d, a.h),
                sptr(W.scale[0], j, d, a.h), sptr(W.scale[1], j, d, a.h), x, x, idx, go, uo, d,
                a.h, a.h, d, dc, dbeg_a(j, u), EPI_SIGMA2, a.act_f32);
       if (a.chain)   // Z already carries the routing weights: unit weight 1
         put_chain(glob(a.cunits) + u, wptr(W.dept_down, j, a.h, d), sptr(W.scale[2], j, a.h, d), zs,
                   a.wdense + (size_t)(m + n) * kChainT, d, s_dtok[j * kTW], u * (d / kstep));
       else
-        put_unit(glob(a.units[3]) + u, wptr(W.dept_down, j, a.h, d), nullptr,
+        put_unit(a.units[3], mu, u, wptr(W.dept_down, j, a.h, d), nullptr,
                  sptr(W.scale[2], j, a.h, d), nullptr, zs, zs, nullptr,
                  a.partial + (size_t)off * a.h, nullptr, a.h, d, d, a.h, dc, dbeg_b(j, u),
                  EPI_STORE, 1, gd);
@@ -983,11 +990,11 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       if (e >= n || my_ec[q] == 0) continue;
       const int u = (s_scan[m + e] >> 16) - ud, off = eoff(e);
       char *yo = static_cast<char *>(a.ybuf) + (size_t)off * d * ab;
-      put_unit(glob(a.units[1]) + u, wptr(W.priv_gate, e, d, d), wptr(W.priv_up, e, d, d),
+      put_unit(a.units[1], mu, u, wptr(W.priv_gate, e, d, d), wptr(W.priv_up, e, d, d),
                sptr(W.scale[3], e, d, d), sptr(W.scale[4], e, d, d), a.gbuf, a.ubuf,
                a.exp_src + off, yo, nullptr, d, d, d, d, my_ec[q], ebeg_a(e, u) - dept_a,
                EPI_SWIGLU, a.act_f32);
-      put_unit(glob(a.units[2]) + u, wptr(W.priv_down, e, d, d), nullptr, sptr(W.scale[5], e, d, d),
+      put_unit(a.units[2], mu, u, wptr(W.priv_down, e, d, d), nullptr, sptr(W.scale[5], e, d, d),
                nullptr, yo, yo, nullptr, a.zbuf + (size_t)off * d, nullptr, d, d, d, d,
                my_ec[q], ebeg_b(e, u) - dept_b, EPI_SIGMA, 1, g2);
     }
@@ -996,7 +1003,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       int units0 = ud, items0 = dept_a, units3 = ud, items3 = dept_b;
       int steps = ud * (d / kstep);
       if (has_se) {
-        put_unit(glob(a.units[0]) + units0, W.se_gate, W.se_up, sptr(W.scale[6], 0, a.d_se, a.h),
+        put_unit(a.units[0], mu, units0, W.se_gate, W.se_up, sptr(W.scale[6], 0, a.d_se, a.h),
                  sptr(W.scale[7], 0, a.d_se, a.h), x, x, nullptr, a.abuf_se, nullptr, a.d_se, a.h,
                  a.h, a.d_se, T, items0, EPI_SWIGLU, a.act_f32);
         if (a.chain) {
@@ -1005,7 +1012,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
                     T >= 32 ? 0xffffffffu : (1u << T) - 1u, steps);
           steps += a.d_se / kstep;
         } else {
-          put_unit(glob(a.units[3]) + units3, W.se_down, nullptr, sptr(W.scale[8], 0, a.h, a.d_se),
+          put_unit(a.units[3], mu, units3, W.se_down, nullptr, sptr(W.scale[8], 0, a.h, a.d_se),
                    nullptr, a.abuf_se, a.abuf_se, nullptr, a.partial + (size_t)ndp * a.h,
                    nullptr, a.h, a.d_se, a.d_se, a.h, T, items3, EPI_STORE, 1, gse);
         }

@@ -184,7 +184,7 @@ void small_route_gate_up_kernel(RouteArgs a) {
     GemmUnit U = {};
     uint32_t mt;
     int sigma = DEAMOE_SIGMA_SILU;
-    U.epi = EPI_SWIGLU;
+    int epi = EPI_SWIGLU;
     if (item < ud * ia_d) {
       const int u = item / ia_d;
       item -= u * ia_d;
@@ -200,7 +200,7 @@ void small_route_gate_up_kernel(RouteArgs a) {
       } else {   // FACTORED: sigma(W_g x) and sigma(W_u x) kept apart
         U.out0 = static_cast<char *>(a.gbuf) + off * a.d_s * ab;
         U.out1 = static_cast<char *>(a.ubuf) + off * a.d_s * ab;
-        U.epi = EPI_SIGMA2;
+        epi = EPI_SIGMA2;
         sigma = a.sigma;
       }
       U.R = a.d_s;
@@ -244,8 +244,7 @@ void small_route_gate_up_kernel(RouteArgs a) {
     U.ldw = h;
     U.ldin = h;
     U.ntok = __popc(mt);
-    U.out_f32 = a.act_f32;
-    U.tpg = 1;
+    U.flags = unit_flags(epi, a.act_f32, 1);
     Run::run(lds.run, &U, item, true, sigma);
   };
   if constexpr (PERSIST) {

@@ -664,3 +664,18 @@ def test_empty_batch_is_a_no_op():
     y = torch.zeros(0, cfg.hidden, device="cuda")
     layer(x, y=y)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("d_private,T,cfg_kw", [
+    (64, 33, {}), (128, 40, {}), (192, 57, dict(d_shared_expert=832)),
+    (64, 128, dict(n_experts=600, n_depts=20, top_k=4)),
+    (128, 36, dict(hidden=4096, n_experts=48)), (128, 70, dict(hidden=4096, w_dtype="bf16"))])
+def test_work_items(d_private, T, cfg_kw):
+    """The stages' work items: one and several K steps per tile, odd and even
+    step counts, several tiles per item, units with one and with several
+    token groups in one launch, more units (up to 620) than one read of the
+    item prefix covers, a router whose last row tile is not full."""
+    kw = dict(cfg_kw)
+    kw.setdefault("n_experts", 40)
+    act = {"bf16": "bf16"}.get(kw.get("w_dtype"), "f32")
+    check_case(Case(small(d_private=d_private, act_dtype=act, **kw), T, seed=80 + T, bias="zipf"))
