@@ -185,10 +185,11 @@ int ntt_of(int T) { return T <= 16 ? 1 : T <= 32 ? 2 : T <= 64 ? 4 : 8; }
 // 363.3 at 72; fp8 645.3 -> 631.1 at 128 but 515.8 -> 531.2 at 96 and 477.2
 // -> 489.3 at 72.  The 2048-wide 7B-class layer was slower with four
 // (145.8 -> 153.1 at 128, before the whole-segment rows): they halve its
-// work items and leave the three-wave two-tile kernel for a two-wave one.  The FACTORED stages keep one tile at
-// every batch: its private gate/up then runs at three waves per SIMD, which
-// outweighs streaming the rows of a unit with more than 16 tokens once per
-// group.
+// work items and leave the three-wave two-tile kernel for a two-wave
+// one.  The FACTORED experts' stage keeps one tile at every batch: it then
+// runs at three waves per SIMD, which outweighs streaming the rows of a unit
+// with more than 16 tokens once per group (its departments' stage:
+// dept_ntt_of).
 int wave_ntt_of(const deamoe_config &c, int T) {
   if (c.form == DEAMOE_FORM_FACTORED) return 1;
   const int four_from = c.w_dtype == DEAMOE_FP8_E4M3_B128 ? 97 : 65;
@@ -237,13 +238,31 @@ int down_groups_max(const deamoe_config &c, int T) {
 // workgroup stream faster.
 int slice_gate_up_ks_of(int T) { return T > kChainT ? 2 : 4; }
 
-// K split of the FACTORED stages: the department gate/up over 4 waves, the
-// private gate/up (split token operands) over 2 (4 was slower at every
+// Token tiles per wave of the FACTORED department gate/up, whose units hold
+// T * top_k_dept / m tokens on average: one up to 16 tokens, then two (K over
+// 4 waves, three waves per SIMD), and on wide layers four (K over 2, two waves
+// per SIMD), so that a department's W_g and W_u stream once per 32 or 64
+// tokens instead of once per 16.  Stage time by trace, us, one tile -> two ->
+// four: Qwen3 (4096 wide) 40.2 -> 36.5 -> 45.7 at 24 tokens, 70.1 -> 55.1 ->
+// 59.1 at 64, 112.1 -> 73.8 -> 68.6 at 128; DeepSeek-V3 112.3 -> 84.8 -> 81.6
+// at 32, 156.7 -> 122.7 -> 97.4 at 64; DeepSeek-V2 (5120) two -> four 50.2 ->
+// 56.0 at 40, 69.9 -> 65.8 at 64; Baseline-7B even at 32 and 64 with two, 9.0
+// -> 12.2 at 64 with four.
+int dept_ntt_of(const deamoe_config &c, int T) {
+  if (T <= kTile) return 1;
+  return (T > 48 && c.hidden >= 5120) || (T > 64 && c.hidden >= 4096) ? 4 : 2;
+}
+int dept_groups_max(const deamoe_config &c, int T) {
+  const int gt = kTile * dept_ntt_of(c, T);
+  return (T + gt - 1) / gt;
+}
+int factored_dept_ks_of(const deamoe_config &c, int T) { return dept_ntt_of(c, T) == 4 ? 2 : 4; }
+
+// K split of the FACTORED private gate/up (split token operands): over 2 waves (4 was slower at every
 // batch), or over none where its contraction (d) is shorter than 1024 and
 // more than 16 tokens give enough tiles (Baseline-7B, d = 384: 143.3 ->
 // 134.0 us per step at 64 tokens; even at 16; the wider Table 1 layers
 // were 1-2 % slower without the split).
-constexpr int kFactoredGateUpKs = 4;
 int factored_priv_ks_of(const deamoe_config &c, int T) {
   return c.d_shared < 1024 && T > 16 ? 1 : 2;
 }
@@ -416,7 +435,8 @@ void fill_route_args(RouteArgs &a, const deamoe_config &c, int T, const void *x,
   a.plan = plan;
   a.down_rows = kDownRows;
   a.down_ks = down_ks_of(c, T);
-  a.wave_tokens = kTile * wave_ntt_of(c, T);
+  a.wave_tokens = kTile * (c.form == DEAMOE_FORM_FACTORED ? dept_ntt_of(c, T) : wave_ntt_of(c, T));
+  a.wave_tokens_e = kTile * wave_ntt_of(c, T);
   a.wave_tokens_b = kTile * down_ntt_of(c, T);
   a.sigma = c.sigma;
   a.part = at<float>(ws, L.part);
@@ -582,8 +602,9 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
     const int d = c.d_shared;
     const int t0 = tiles_bound(act_depts, d) + se * tiles_bound(1, c.d_shared_expert);
     if (!small)
-      DEAMOE_TRY(launch_grouped_gemm(stage(0, act_depts + se), wt, 2, GEMM_PLAIN, ntt, kFactoredGateUpKs, t0 * groups,
-                                     kGridCap, s));
+      DEAMOE_TRY(launch_grouped_gemm(stage(0, act_depts + se), wt, 2, GEMM_PLAIN, dept_ntt_of(c, T),
+                                     factored_dept_ks_of(c, T), t0 * dept_groups_max(c, T),
+                                     kGridCap, s, true));
     if (c.sigma == DEAMOE_SIGMA_RMSNORM) {   // timed with stage 0
       RowNormArgs na;
       na.counts = pc;

@@ -77,7 +77,8 @@ __global__ __launch_bounds__(256) void grouped_gemm_kernel(GemmStage st) {
 //  - bf16 and fp32 stages with two token tiles whose token operand is
 //    requested per step (B1): row pairs (same-process A/B at the DeepSeek-V3
 //    shape, down stage at 128 tokens 378.3 -> 370.0 us, skewed 178.9 ->
-//    172.8), and gate/up pairs of layers narrower than 4096 (the 7B-class
+//    172.8), the FACTORED department gate/up (dept_ntt_of), and gate/up
+//    pairs of SLICE layers narrower than 4096 (the 7B-class
 //    layer 48.5 -> 44.9 us at 32 tokens, 52.3 -> 48.5 at 64; at the
 //    DeepSeek-V3 shape they were 0-2 % slower, so two waves stay there).
 template <int WT, int NW, int NTT, int KS, bool SPLIT, bool PAIR, bool B1>
@@ -98,10 +99,10 @@ void grouped_gemm_wide_kernel(GemmStage st) {
 }
 
 // mode: GemmMode; row pairs exist for NTT <= 2 only (the host picks them so).
-// narrow: two-token-tile gate/up pairs run at three waves per SIMD.
+// three: two-token-tile gate/up pairs run at three waves per SIMD.
 template <int WT, int NW, int NTT, int KS>
 static hipError_t launch_gemm(const GemmStage &st, int mode, int max_tiles, int grid_cap,
-                              bool narrow, hipStream_t s) {
+                              bool three, hipStream_t s) {
   constexpr int TPB = 4 / KS;
   int grid = (max_tiles + TPB - 1) / TPB;
   grid = grid < 1 ? 1 : (grid > grid_cap ? grid_cap : grid);
@@ -135,7 +136,7 @@ static hipError_t launch_gemm(const GemmStage &st, int mode, int max_tiles, int 
     if constexpr (NTT == 2 && KS > 1) {
       if constexpr (FP8)
         return plain(grouped_gemm_occ3_kernel<WT, NW, NTT, KS, false, false, KS == 2>);
-      else if (narrow)
+      else if (three)
         return plain(grouped_gemm_occ3_kernel<WT, NW, NTT, KS, false, false, true>);
     }
   }
@@ -146,12 +147,12 @@ static hipError_t launch_gemm(const GemmStage &st, int mode, int max_tiles, int 
 // token sets are split into groups).
 template <int WT, int NW, int KS>
 static hipError_t dispatch_ntt(const GemmStage &st, int mode, int ntt, int max_tiles, int cap,
-                               bool narrow, hipStream_t s) {
+                               bool three, hipStream_t s) {
   switch (ntt) {
-    case 1: return launch_gemm<WT, NW, 1, KS>(st, mode, max_tiles, cap, narrow, s);
-    case 2: return launch_gemm<WT, NW, 2, KS>(st, mode, max_tiles, cap, narrow, s);
+    case 1: return launch_gemm<WT, NW, 1, KS>(st, mode, max_tiles, cap, three, s);
+    case 2: return launch_gemm<WT, NW, 2, KS>(st, mode, max_tiles, cap, three, s);
     case 4:   // gate/up with a K split over 2 waves, row pairs without one
-      if constexpr (KS <= 2) return launch_gemm<WT, NW, 4, KS>(st, mode, max_tiles, cap, narrow, s);
+      if constexpr (KS <= 2) return launch_gemm<WT, NW, 4, KS>(st, mode, max_tiles, cap, three, s);
       return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
@@ -159,21 +160,21 @@ static hipError_t dispatch_ntt(const GemmStage &st, int mode, int ntt, int max_t
 
 template <int WT, int NW>
 static hipError_t dispatch_ks(const GemmStage &st, int mode, int ntt, int ks, int max_tiles,
-                              int cap, bool narrow, hipStream_t s) {
+                              int cap, bool three, hipStream_t s) {
   switch (ks) {
-    case 1: return dispatch_ntt<WT, NW, 1>(st, mode, ntt, max_tiles, cap, narrow, s);
-    case 2: return dispatch_ntt<WT, NW, 2>(st, mode, ntt, max_tiles, cap, narrow, s);
-    default: return dispatch_ntt<WT, NW, 4>(st, mode, ntt, max_tiles, cap, narrow, s);
+    case 1: return dispatch_ntt<WT, NW, 1>(st, mode, ntt, max_tiles, cap, three, s);
+    case 2: return dispatch_ntt<WT, NW, 2>(st, mode, ntt, max_tiles, cap, three, s);
+    default: return dispatch_ntt<WT, NW, 4>(st, mode, ntt, max_tiles, cap, three, s);
   }
 }
 
 hipError_t launch_grouped_gemm(const GemmStage &st, int wtype, int nw, int mode, int ntt,
-                               int ks, int max_tiles, int grid_cap, hipStream_t s, bool narrow) {
+                               int ks, int max_tiles, int grid_cap, hipStream_t s, bool three) {
   if (nw != 2) return hipErrorInvalidValue;   // every stage streams two matrices or a row pair
   switch (wtype) {
-    case WT_F32: return dispatch_ks<WT_F32, 2>(st, mode, ntt, ks, max_tiles, grid_cap, narrow, s);
-    case WT_BF16: return dispatch_ks<WT_BF16, 2>(st, mode, ntt, ks, max_tiles, grid_cap, narrow, s);
-    default: return dispatch_ks<WT_FP8, 2>(st, mode, ntt, ks, max_tiles, grid_cap, narrow, s);
+    case WT_F32: return dispatch_ks<WT_F32, 2>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
+    case WT_BF16: return dispatch_ks<WT_BF16, 2>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
+    default: return dispatch_ks<WT_FP8, 2>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
   }
 }
 

@@ -41,6 +41,7 @@ struct RouteArgs {
   int32_t down_rows;     // weight rows of a down-projection tile (16, or 32 for row pairs)
   int32_t down_ks;       // waves sharing one down-projection tile (K split)
   int32_t wave_tokens;   // tokens of one token group of the gate/up stages (16 * NTT)
+  int32_t wave_tokens_e; // the same for the FACTORED experts' gate/up stage
   int32_t wave_tokens_b; // the same for the down stages
   int32_t sigma;         // DEAMOE_SIGMA_* of the FACTORED gate/up stage
   // logits: sum of kc partial products, or injected; optional bias
@@ -119,12 +120,11 @@ enum GemmMode : int {
   GEMM_PAIR = 2,    // the "two matrices" are adjacent 16-row tiles of one matrix
 };
 // max_tiles bounds the stage's work items (row tiles of kTile rows, or of
-// 2 * kTile rows in GEMM_PAIR mode) for the grid size.  narrow: a gate/up
-// stage of a layer narrower than 4096 (two token tiles then run at three
-// waves per SIMD).
+// 2 * kTile rows in GEMM_PAIR mode) for the grid size.  three: a gate/up
+// stage with two token tiles runs at three waves per SIMD.
 hipError_t launch_grouped_gemm(const GemmStage &st, int wtype, int nw, int mode, int ntt,
                                int ks, int max_tiles, int grid_cap, hipStream_t s,
-                               bool narrow = false);
+                               bool three = false);
 hipError_t launch_combine(const CombineArgs &a, hipStream_t s);
 // SLICE batches of 1..4 tokens with the fused down kernel (a.chain): routing,
 // the gate/up stage and the down kernel's units in one launch (items: the

@@ -820,9 +820,13 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
   // token groups of a unit: wave_tokens per group in the gate/up stages (pair
   // A), wave_tokens_b in the separate down stages (pair B; the fused down
   // kernel takes one group, and reads the bitmaps the item scans would reuse)
-  const int wt = a.wave_tokens, wtb = a.chain ? wt : a.wave_tokens_b;
-  const bool multi = T > min(wt, wtb);
+  // (FACTORED: wave_tokens in the department stage, wave_tokens_e in the
+  // experts')
+  const int wt = a.wave_tokens, wte = a.wave_tokens_e;
+  const int wtb = a.chain ? wt : a.wave_tokens_b;
+  const bool multi = T > min(min(wt, wte), wtb);
   auto groups = [&](int cnt) { return T > wt ? (cnt + wt - 1) / wt : 1; };
+  auto groups_e = [&](int cnt) { return T > wte ? (cnt + wte - 1) / wte : 1; };
   auto groups_b = [&](int cnt) { return T > wtb ? (cnt + wtb - 1) / wtb : 1; };
   int32_t *s_ia = reinterpret_cast<int32_t *>(s_etok);           // [m + n] items, stage pair A
   int32_t *s_ib = s_ia + kMaxM + kMaxN;                           // [m + n] items, stage pair B
@@ -860,7 +864,7 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
       const int e = tid + q * BT;
       if (e < n) {
         const bool act = has_priv && my_ec[q] > 0;
-        s_ia[m + e] = act ? ia_e * groups(my_ec[q]) : 0;
+        s_ia[m + e] = act ? ia_e * groups_e(my_ec[q]) : 0;
         s_ib[m + e] = act ? ib_e * groups_b(my_ec[q]) : 0;
       }
     }

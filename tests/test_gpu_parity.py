@@ -679,3 +679,18 @@ def test_work_items(d_private, T, cfg_kw):
     kw.setdefault("n_experts", 40)
     act = {"bf16": "bf16"}.get(kw.get("w_dtype"), "f32")
     check_case(Case(small(d_private=d_private, act_dtype=act, **kw), T, seed=80 + T, bias="zipf"))
+
+
+@pytest.mark.parametrize("hidden,w_dtype,T,cfg_kw", [
+    (512, "bf16", 17, {}), (512, "f32", 33, {}), (1024, "fp8", 50, {}),
+    (4096, "bf16", 64, {}), (4096, "bf16", 65, dict(d_shared_expert=128)),
+    (5120, "bf16", 48, {}), (5120, "f32", 49, {}), (5120, "fp8", 128, dict(d_shared_expert=256)),
+    (4096, "bf16", 128, dict(sigma="rmsnorm", top_k=4, top_k_dept=2))])
+def test_factored_department_tiles(hidden, w_dtype, T, cfg_kw):
+    """The FACTORED department gate/up with one, two and four token tiles:
+    the batches and widths where the rule changes, departments of more than
+    one token group beside nearly empty ones (skewed), the shared expert."""
+    act = "f32" if w_dtype == "f32" else "bf16"
+    cfg = small(form="factored", hidden=hidden, d_shared=128, d_private=0, w_dtype=w_dtype,
+                act_dtype=act, **cfg_kw)
+    check_case(Case(cfg, T, seed=90 + T, bias="zipf"))
