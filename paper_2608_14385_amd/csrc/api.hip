@@ -202,9 +202,10 @@ int token_groups_max(const deamoe_config &c, int T) {
 // Token tiles per wave in the separate down stages (above 32 tokens for
 // SLICE).  Layers narrower than 4096 keep one tile up to 56 tokens: there
 // the one-tile row pairs at three waves per SIMD outweigh streaming the rows
-// of a unit with more than 16 tokens once per group (same-process A/B with
-// the token rows loaded as whole segments, us per step, one tile -> two: the
-// 7B-class layer 84.0 -> 91.3 at 40 tokens, 85.3 -> 92.2 at 52, 87.9 ->
+// of a unit with more than 16 tokens once per group (with K split over two
+// waves, two tiles -> one, the 7B-class layer 87.4 -> 91.1 us per step at 61
+// tokens and even at 40; before the split, same-process A/B, one tile -> two:
+// 84.0 -> 91.3 at 40 tokens, 85.3 -> 92.2 at 52, 87.9 ->
 // 92.9 at 56, but 96.3 -> 94.2 at 60 and 98.9 -> 96.9 at 64; before those
 // rows two tiles lost at 64 too, 106.2 -> 110.5).  Wider layers take two
 // (the DeepSeek-V3 shape 776.5 -> 775.3 at 56, 819.6 -> 806.3 at 64; fp8
@@ -272,8 +273,10 @@ int factored_priv_ks_of(const deamoe_config &c, int T) {
 constexpr int kDownRows = 2 * kTile;
 
 // Waves sharing one down-projection tile.  The SLICE form packs several
-// short private tiles per work item and keeps whole tiles per wave (K split
-// over two waves up to two tokens, where the batch leaves few work items);
+// short private tiles per work item and keeps whole tiles per wave, with K
+// split over two waves up to two tokens, where the batch leaves few work
+// items, and on layers narrower than 4096 (long contractions only,
+// down_split_k_of);
 // the FACTORED form (every contraction d long) splits K four ways up to 8
 // tokens and two ways up to 32 (64 where h >= 4096), while the batch leaves
 // too few tiles to occupy the waves.  From 9 to 16 tokens the split follows
@@ -282,7 +285,7 @@ constexpr int kDownRows = 2 * kTile;
 // 698.6, Kimi-K2 852.2 -> 846.2, Baseline-7B 71.5 -> 70.2; Qwen3 and
 // DeepSeek-V2, d = 1536, were even either way).
 int down_ks_of(const deamoe_config &c, int T) {
-  if (c.form == DEAMOE_FORM_SLICE) return T <= 2 ? 2 : 1;
+  if (c.form == DEAMOE_FORM_SLICE) return T <= 2 || c.hidden < 4096 ? 2 : 1;
   if (T <= 8) return 4;
   if (T <= 16 && c.d_shared >= 2048) return 4;
   if (T <= 16 && c.d_shared < 1024) return 1;
@@ -290,6 +293,20 @@ int down_ks_of(const deamoe_config &c, int T) {
   return T <= 32 || (wide && T <= 64) ? 2 : 1;
 }
 
+
+// Shortest contraction that the K split of a down stage is for.  Layers
+// narrower than 4096 have few tiles, and without a split one wave streams all
+// K steps of a tile (22 in the 7B-class shared expert, the launch's critical
+// path); their short private contractions keep whole tiles per wave, several
+// to an item, which the split would leave waves without work.  Same-process
+// A/B against no split, us per step: the 7B-class layer 80.7 -> 69.5 at 25
+// tokens, 81.6 -> 76.5 at 40, 95.6 -> 87.4 at 61, 120.1 -> 114.1 at 128; the
+// 256-wide fp32 layer 45.4 -> 39.5 at 40.  Wider layers were even (the
+// DeepSeek-V3 shape 784.3 -> 784.3 at 64) or slower (fp8 404.7 -> 407.3 at
+// 45) and keep whole tiles.
+int down_split_k_of(const deamoe_config &c, int T) {
+  return c.form == DEAMOE_FORM_SLICE && T > 2 ? 512 : 0;
+}
 
 // Down projections and combine fused into one kernel (the SLICE down stage,
 // the FACTORED department down stage): batches whose active units fit the
@@ -435,6 +452,7 @@ void fill_route_args(RouteArgs &a, const deamoe_config &c, int T, const void *x,
   a.plan = plan;
   a.down_rows = kDownRows;
   a.down_ks = down_ks_of(c, T);
+  a.down_split_k = down_split_k_of(c, T);
   a.wave_tokens = kTile * (c.form == DEAMOE_FORM_FACTORED ? dept_ntt_of(c, T) : wave_ntt_of(c, T));
   a.wave_tokens_e = kTile * wave_ntt_of(c, T);
   a.wave_tokens_b = kTile * down_ntt_of(c, T);

@@ -253,7 +253,7 @@ __device__ inline void tile_loop(const GemmUnit &U, int rt0, int nsub, int kp, i
   const int nsteps = uniform(U.K / Tr::K_STEP);
   const int nloc = kp < nsteps ? (nsteps - kp + ks - 1) / ks : 0;   // K steps of this wave per tile
   const int total = nloc * nsub;
-  if (total == 0) return;
+  if (total <= 0) return;
   const int ntok = uniform(U.ntok) - tok0;   // tokens of this item: tok0 .. U.ntok - 1
   // ROWS: the token operand of two or more tiles is loaded like the weights,
   // as whole 256-byte row segments (instruction q of tile tt covers tokens
@@ -531,6 +531,9 @@ template <int WT, int NW, int NTT, int KS, bool SPLIT = false, bool PAIR = false
 struct TileRunner {
   static constexpr int TR = PAIR ? 2 * kTile : kTile;   // weight rows of a tile
   static constexpr int TPB = 4 / KS;
+  // row pairs split over two waves: a unit may instead give each wave tiles of
+  // its own (units with a short contraction beside long ones)
+  static constexpr bool MIX = PAIR && KS == 2;
   static constexpr int STAGE_BYTES = NW * WLoad<WT>::REGION;   // per wave
   static constexpr int RED_BYTES = KS > 1 ? NW * NTT * kWave * 16 : 0;   // per wave
   static constexpr int WAVE_BYTES = STAGE_BYTES > RED_BYTES ? STAGE_BYTES : RED_BYTES;
@@ -550,10 +553,14 @@ struct TileRunner {
 #pragma unroll
       for (int tt = 0; tt < NTT; ++tt) acc[n][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
     int rt0 = 0, nsub = 1, tok0 = 0;
+    bool split = KS > 1;   // the item's waves share its K steps
     if (active) {
       constexpr int GT = kTile * NTT;   // tokens of a group
       const int groups = (uniform(U->ntok) + GT - 1) / GT;
-      const int tpg = KS == 1 ? unit_tpg(uniform(U->flags)) : 1;
+      const int fl = unit_tpg(uniform(U->flags));
+      split = KS > 1 && !(MIX && fl > 0);
+      const int own = split ? 1 : fl;              // tiles of a wave
+      const int tpg = KS > 1 && !split ? KS * fl : own;   // tiles of the item
       const int ntiles = (uniform(U->R) + TR - 1) / TR;
       if (groups > 1) {
         // The token groups of one tile item stream the same weight rows.
@@ -578,8 +585,8 @@ struct TileRunner {
         tok0 = uniform(g) * GT;
         item = uniform(ti);
       }
-      rt0 = item * tpg;
-      nsub = min(tpg, ntiles - rt0);
+      rt0 = item * tpg + (split || KS == 1 ? 0 : kp * own);
+      nsub = min(own, ntiles - rt0);   // 0 or less: no tiles left for this wave
       auto done = [&](int rt, const f32x4 (&a)[NW][NTT]) {
         tile_epilogue<NW, NTT, PAIR>(*U, rt, tok0, sigma, a);
       };
@@ -589,30 +596,31 @@ struct TileRunner {
       // other weight row is read once and streams past them.
       const int ntok = uniform(U->ntok) - tok0;
       const int ntt = uniform(min(NTT, (ntok + kTile - 1) / kTile));
-      constexpr bool MULTI = KS == 1;
+      constexpr bool MULTI = KS == 1 || MIX;
+      const int lp = split ? kp : 0, ls = split ? KS : 1;
       if (groups > 1)
-        tile_loop<WT, NW, NTT, NTT, SPLIT, PAIR, false, B1, MULTI>(*U, rt0, nsub, kp, KS, tok0, ntt,
+        tile_loop<WT, NW, NTT, NTT, SPLIT, PAIR, false, B1, MULTI>(*U, rt0, nsub, lp, ls, tok0, ntt,
                                                                    sm.buf[wave], acc, done);
       else if (NTT == 2 && !B1 && ntt == 1)
         // a one-tile loop of its own: with the second tile's loads optional,
         // a wait for them would have to count the shortest case and so wait
         // for part of the next group's weights
-        tile_loop<WT, NW, NTT, 1, SPLIT, PAIR, true, B1, MULTI>(*U, rt0, nsub, kp, KS, tok0, ntt,
+        tile_loop<WT, NW, NTT, 1, SPLIT, PAIR, true, B1, MULTI>(*U, rt0, nsub, lp, ls, tok0, ntt,
                                                                 sm.buf[wave], acc, done);
       else
         tile_loop<WT, NW, NTT, NTT, SPLIT, PAIR, true, B1, MULTI>(
-            *U, rt0, nsub, kp, KS, tok0, NTT == 2 && !B1 ? 2 : ntt, sm.buf[wave], acc, done);
+            *U, rt0, nsub, lp, ls, tok0, NTT == 2 && !B1 ? 2 : ntt, sm.buf[wave], acc, done);
     }
     if constexpr (KS > 1) {
       f32x4 *red = reinterpret_cast<f32x4 *>(sm.buf[wave]);
-      if (active && kp > 0) {
+      if (active && split && kp > 0) {
 #pragma unroll
         for (int n = 0; n < NW; ++n)
 #pragma unroll
           for (int tt = 0; tt < NTT; ++tt) red[(n * NTT + tt) * kWave + lane] = acc[n][tt];
       }
       __syncthreads();
-      if (active && kp == 0) {
+      if (active && split && kp == 0) {
         for (int q = 1; q < KS; ++q) {
           const f32x4 *r = reinterpret_cast<const f32x4 *>(sm.buf[wave + q]);
 #pragma unroll
@@ -623,7 +631,7 @@ struct TileRunner {
       }
       __syncthreads();
     }
-    if (active && kp == 0 && nsub == 1) tile_epilogue<NW, NTT, PAIR>(*U, rt0, tok0, sigma, acc);
+    if (active && (kp == 0 || !split) && nsub == 1) tile_epilogue<NW, NTT, PAIR>(*U, rt0, tok0, sigma, acc);
   }
 };
 

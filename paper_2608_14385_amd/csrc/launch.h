@@ -40,6 +40,7 @@ struct RouteArgs {
   int32_t h, d_s, d_p, d_se, act_f32, w_bytes, fp8, plan;
   int32_t down_rows;     // weight rows of a down-projection tile (16, or 32 for row pairs)
   int32_t down_ks;       // waves sharing one down-projection tile (K split)
+  int32_t down_split_k;  // shortest contraction that split is for (one below it: no split)
   int32_t wave_tokens;   // tokens of one token group of the gate/up stages (16 * NTT)
   int32_t wave_tokens_e; // the same for the FACTORED experts' gate/up stage
   int32_t wave_tokens_b; // the same for the down stages

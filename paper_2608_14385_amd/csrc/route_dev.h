@@ -218,15 +218,21 @@ __device__ inline void put_chain(gmem<ChainUnit> *U, const void *w, const float 
   U->pad_ = 0;
 }
 
-// Row tiles per work item of a stage whose K is not split across waves: short
-// contractions take several tiles so that a work item streams enough bytes.
-__device__ inline int tiles_per_item(int K, int rows, int ks) {
-  if (ks > 1) return 1;
+// Row tiles of a stage's work items.  A wave that holds whole tiles (K not
+// split) takes several of a short contraction, so that it streams enough
+// bytes.  With a K split over ks waves an item is one tile, except in units
+// whose K is shorter than split_k: there each wave takes tiles of its own.
+struct ItemTiles {
+  int item;   // tiles of a work item
+  int flag;   // tiles of a wave for unit_flags, 0: the item's waves share its K steps
+};
+__device__ inline ItemTiles tiles_per_item(int K, int rows, int ks, int split_k) {
+  if (ks > 1 && K >= split_k) return {1, 0};
   int t = max(1, min(8, 2048 * kTile / (rows * K)));
-  // fp8: the item's block scales, (t * rows / 128 + 1) scale rows of K / 128,
+  // fp8: a wave's block scales, (t * rows / 128 + 1) scale rows of K / 128,
   // fit the 64-entry window of a work item
   while (t > 1 && (t * rows / 128 + 1) * (K / 128) > 64) --t;
-  return t;
+  return {t * ks, t};
 }
 __device__ inline int items_of(int R, int tpg, int rows) {
   return ((R + rows - 1) / rows + tpg - 1) / tpg;
@@ -830,18 +836,19 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
   auto groups_b = [&](int cnt) { return T > wtb ? (cnt + wtb - 1) / wtb : 1; };
   int32_t *s_ia = reinterpret_cast<int32_t *>(s_etok);           // [m + n] items, stage pair A
   int32_t *s_ib = s_ia + kMaxM + kMaxN;                           // [m + n] items, stage pair B
-  const int dr = a.down_rows, dk = a.down_ks;
+  const int dr = a.down_rows, dk = a.down_ks, sk = a.down_split_k;
   // items per row-tile item: (A dept, A expert, B dept, B expert)
   int ia_d, ia_e, ib_d, ib_e;
   if (slice) {
-    const int gd = tiles_per_item(a.d_s, dr, dk), gp = a.d_p ? tiles_per_item(a.d_p, dr, dk) : 1;
+    const int gd = tiles_per_item(a.d_s, dr, dk, sk).item;
+    const int gp = a.d_p ? tiles_per_item(a.d_p, dr, dk, sk).item : 1;
     ia_d = (a.d_s + kTile - 1) / kTile;
     ia_e = has_priv ? (a.d_p + kTile - 1) / kTile : 0;
     ib_d = items_of(a.h, gd, dr);
     ib_e = has_priv ? items_of(a.h, gp, dr) : 0;
   } else {
     const int d = a.d_s;
-    const int gd = tiles_per_item(d, dr, dk), g2 = tiles_per_item(d, dr, dk);
+    const int gd = tiles_per_item(d, dr, dk, sk).item, g2 = gd;
     ia_d = (d + kTile - 1) / kTile;   // stage 0: W_g, W_u
     ia_e = ia_d;                      // stage 1: A_g, A_u
     ib_d = items_of(a.h, gd, dr);     // stage 3: W_d^T
@@ -886,9 +893,10 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
   const int dept_b = scanned ? s_ib[m] : ud * ib_d;
   const int kstep = a.w_bytes == 4 ? 64 : 128;   // K step of the weight type
   if (slice) {
-    const int gd = tiles_per_item(a.d_s, dr, dk), gp = a.d_p ? tiles_per_item(a.d_p, dr, dk) : 1;
-    const int gse = a.d_se ? tiles_per_item(a.d_se, dr, dk) : 1;
-    const int bse = items_of(a.h, gse, dr);
+    const int gd = tiles_per_item(a.d_s, dr, dk, sk).flag;
+    const int gp = a.d_p ? tiles_per_item(a.d_p, dr, dk, sk).flag : 0;
+    const ItemTiles se = a.d_se ? tiles_per_item(a.d_se, dr, dk, sk) : ItemTiles{1, 0};
+    const int gse = se.flag, bse = items_of(a.h, se.item, dr);
     // fused down stage (T <= 32): the units' K steps are concatenated in
     // table order (departments, experts, the shared expert)
     const int sd = a.d_s / kstep, sp = a.d_p / kstep;
@@ -964,9 +972,10 @@ __device__ __attribute__((always_inline)) void plan_body(const RouteArgs &a, PS 
     }
   } else {  // PLAN_FACTORED
     const int d = a.d_s;
-    const int gd = tiles_per_item(d, dr, dk), gse = a.d_se ? tiles_per_item(a.d_se, dr, dk) : 1;
-    const int bse = items_of(a.h, gse, dr);
-    const int g2 = tiles_per_item(d, dr, dk);   // A_d^T: d x d, streamed like the down projections
+    const int gd = tiles_per_item(d, dr, dk, sk).flag;
+    const int g2 = gd;   // A_d^T: d x d, streamed like the down projections
+    const ItemTiles se = a.d_se ? tiles_per_item(a.d_se, dr, dk, sk) : ItemTiles{1, 0};
+    const int gse = se.flag, bse = items_of(a.h, se.item, dr);
 #pragma unroll
     for (int q = 0; q < DPT; ++q) {
       const int j = tid + q * BT, dc = my_dc[q];

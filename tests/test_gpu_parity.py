@@ -694,3 +694,18 @@ def test_factored_department_tiles(hidden, w_dtype, T, cfg_kw):
     cfg = small(form="factored", hidden=hidden, d_shared=128, d_private=0, w_dtype=w_dtype,
                 act_dtype=act, **cfg_kw)
     check_case(Case(cfg, T, seed=90 + T, bias="zipf"))
+
+
+@pytest.mark.parametrize("hidden,w_dtype,T,d_shared,d_private,d_se", [
+    (256, "f32", 33, 512, 64, 448), (2176, "bf16", 29, 640, 128, 512),
+    (2176, "bf16", 57, 384, 128, 896), (1024, "fp8", 40, 512, 128, 384),
+    (1152, "fp8", 128, 1024, 256, 0), (512, "f32", 100, 576, 512, 64)])
+def test_narrow_down_split(hidden, w_dtype, T, d_shared, d_private, d_se):
+    """The separate down stage of narrow layers: long contractions split over
+    two waves beside short ones that give each wave tiles of its own (both
+    sides of 512), item counts that leave the last wave fewer tiles or none,
+    one and two token tiles, several token groups."""
+    act = "f32" if w_dtype == "f32" else "bf16"
+    cfg = small(hidden=hidden, w_dtype=w_dtype, act_dtype=act, d_shared=d_shared,
+                d_private=d_private, d_shared_expert=d_se, n_experts=40, top_k=3)
+    check_case(Case(cfg, T, seed=100 + T, bias="zipf"))
