@@ -26,7 +26,9 @@ __global__ __launch_bounds__(256) void router_kernel(RouterArgs a) {
   using Run = TileRunner<WT, 1, NTT, 4>;
   __shared__ typename Run::Smem sm;
   using Tr = WTraits<WT>;
-  const int rt = blockIdx.x % a.tiles, c = blockIdx.x / a.tiles;
+  // more than 16 * NTT tokens: one work item per token group of a tile
+  const int items = a.tiles * ((a.T + kTile * NTT - 1) / (kTile * NTT));
+  const int it = blockIdx.x % items, c = blockIdx.x / items;
   GemmUnit U = {};
   U.w0 = static_cast<const char *>(a.w) + (size_t)c * a.kchunk * Tr::W_BYTES;
   U.in0 = U.in1 = static_cast<const char *>(a.x) + (size_t)c * a.kchunk * Tr::A_BYTES;
@@ -39,17 +41,16 @@ __global__ __launch_bounds__(256) void router_kernel(RouterArgs a) {
   U.ldout = a.ldp;
   U.ntok = a.T;
   U.flags = unit_flags(EPI_STORE, 1, 1);
-  Run::run(sm, &U, rt, true, DEAMOE_SIGMA_NONE);
+  Run::run(sm, &U, it, true, DEAMOE_SIGMA_NONE);
 }
 
 template <int WT>
 static hipError_t router_ntt(const RouterArgs &a, int ntt, int kc, hipStream_t s) {
-  dim3 grid(a.tiles * kc);
+  dim3 grid(a.tiles * kc * ((a.T + kTile * ntt - 1) / (kTile * ntt)));
   switch (ntt) {
     case 1: hipLaunchKernelGGL((router_kernel<WT, 1>), grid, dim3(256), 0, s, a); break;
     case 2: hipLaunchKernelGGL((router_kernel<WT, 2>), grid, dim3(256), 0, s, a); break;
-    case 4: hipLaunchKernelGGL((router_kernel<WT, 4>), grid, dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((router_kernel<WT, 8>), grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((router_kernel<WT, 4>), grid, dim3(256), 0, s, a); break;
   }
   return hipGetLastError();
 }
