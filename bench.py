@@ -39,9 +39,9 @@ HBM_PEAK_GBPS = 8000.0
 #  - the average launch duration from a kernel-trace run of the default
 #    command (profiles/gate_up_dsv3_bf16_T16_kernel_trace.md), which excludes
 #    the launch gap that the benchmark's own events include.
-TRAFFIC_BYTES = 2341123891
-PROFILED_GATE_UP_US = 339.66
-TRAFFIC_SOURCES_SHA256 = "642b1e82bc6283e4a1c664beac1f39abd57d15368ba13a966b2f9276ae23cdce"
+TRAFFIC_BYTES = 2341200282
+PROFILED_GATE_UP_US = 359.44
+TRAFFIC_SOURCES_SHA256 = "395db81b1c53e23bb0f22db2b00e3a8fa831a1e687a8f918626e92a1cb08a662"
 
 
 def library_sources_digest() -> str:
