@@ -168,7 +168,7 @@ def test_fused_down_row_blocks(hidden, w_dtype, T):
 @pytest.mark.parametrize("d_shared,T", [(640, 6), (1088, 5), (1152, 5)])
 def test_fused_down_narrow_steps(d_shared, T):
     """Layers narrower than 2048 above 4 tokens: fused while a step has at
-    most 96 K steps (640: 56 at 6 tokens; 1088 and 1152: 83 and 87 at 5), the
+    most 96 K steps (640: 56 at 6 tokens; 1088 and 1152: 82 and 86 at 5), the
     separate stage beyond (d_private 512 below)."""
     check_case(Case(small(d_shared=d_shared, d_private=64, d_shared_expert=256), T, seed=70))
     check_case(Case(small(d_shared=d_shared, d_private=512, top_k=3), T, seed=71))
