@@ -336,8 +336,7 @@ int down_split_k_of(const deamoe_config &c, int T) {
 // DeepSeek-V2 (h = 5120) 90.3 -> 86.6 at one token, 389.7 -> 389.0 at 16.
 constexpr int kChainMinTiles = 128, kChainMinTilesFactored = 32;
 constexpr int kChainNarrowMinTiles = 64, kChainNarrowMaxT = 24, kChainNarrowSteps = 96;
-// Units (and SLICE K steps) of the fused kernel a step of T tokens can have
-// at most.
+// Units and K steps of the fused kernel a step of T tokens can have at most.
 struct ChainBound {
   int units, steps;
 };
@@ -614,6 +613,7 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       ch.h = c.hidden;
       ch.act_f32 = c.act_dtype == DEAMOE_F32;
       ch.max_units = chain_bound(c, T).units;
+      ch.max_steps = chain_bound(c, T).steps;
       DEAMOE_TRY(launch_chain(ch, wt, s));
       DEAMOE_TRY(ev.mark());
       return DEAMOE_OK;
@@ -671,6 +671,7 @@ int layer_impl(const deamoe_config *cfg, int32_t T, const void *x, const deamoe_
       ch.h = c.hidden;
       ch.act_f32 = c.act_dtype == DEAMOE_F32;
       ch.max_units = chain_bound(c, T).units;
+      ch.max_steps = chain_bound(c, T).steps;
       DEAMOE_TRY(launch_chain(ch, wt, s));
       DEAMOE_TRY(ev.mark());
       return DEAMOE_OK;

@@ -256,12 +256,13 @@ __global__ __launch_bounds__(KSC * kWave) void chain_down_kernel(ChainArgs a) {
   }
 }
 
+// 8 waves per workgroup, each streaming one contiguous range of the
+// concatenated K steps, one load group in flight while one is multiplied.
+constexpr int kChainWaves = 8;
+
 template <int WT, int NW, int P, int NTT>
 static hipError_t launch_chain_wt(const ChainArgs &a, hipStream_t s) {
-  constexpr int TR = NW * kTile / P;
-  // 8 waves per workgroup, each streaming one contiguous range of the
-  // concatenated K steps, one load group in flight while one is multiplied
-  constexpr int KSC = 8;
+  constexpr int TR = NW * kTile / P, KSC = kChainWaves;
   hipLaunchKernelGGL((chain_down_kernel<WT, NW, P, NTT, KSC>), dim3((a.h + TR - 1) / TR),
                      dim3(KSC * kWave), 0, s, a);
   return hipGetLastError();
@@ -282,14 +283,23 @@ constexpr int kChainPairMinH = 5120;
 // latency: 12 or 16 waves on 128 CUs were no faster.  Kernel time by trace,
 // us, 16 rows -> 8: the 7B-class layer 10.0 -> 8.4 at one token, 16.4 -> 13.7
 // at 5, 22.2 -> 18.6 at 16, 29.5 -> 26.9 at 24; Baseline-7B (1024 wide) 6.3
-// -> 5.5 at 16, 4.6 -> 5.2 at one token.  At 4096 (Qwen3, 512 workgroups in
-// two rounds) 8 rows lost: 18.9 -> 25.2 at 16, and 4 rows lost at 2048 too.
-constexpr int kChainSplitMaxH = 2048;
+// -> 5.5 at 16.  At 4096 (Qwen3, 512 workgroups in two rounds) 8 rows lost:
+// 18.9 -> 25.2 at 16, and 4 rows lost at 2048 too.
+// A step of fewer than kChainSplitSteps K steps keeps 16 rows: a wave then has
+// two or three steps at most, which a 16-row wave requests at once, and the
+// pairs only double the matrix products and the prologue's work.  Step times,
+// us, 8 rows -> 16: Baseline-7B FACTORED at one token (at most 12 steps) 33.7
+// -> 33.3; 1024-wide layers of 8 steps at one token 14.9 -> 14.4 (bf16) and
+// 14.7 -> 14.3 (fp8), of 16 (fp32) 17.8 -> 16.3; 8 steps, 2048 wide, 30.6 ->
+// 27.9 at 20 tokens.  From 24 steps on 8 rows gain: the Baseline-7B vanilla
+// layer at one token (24) 18.3 -> 17.7, the 7B-class layer (at most 82) 33.6
+// -> 32.4.
+constexpr int kChainSplitMaxH = 2048, kChainSplitSteps = 3 * kChainWaves;
 
 template <int WT>
 static hipError_t launch_chain_ntt(const ChainArgs &a, hipStream_t s) {
   const bool one = a.T <= kTile;
-  if (a.h <= kChainSplitMaxH)
+  if (a.h <= kChainSplitMaxH && a.max_steps >= kChainSplitSteps)
     return one ? launch_chain_wt<WT, 1, 2, 1>(a, s) : launch_chain_wt<WT, 1, 2, 2>(a, s);
   if (a.h < kChainPairMinH)
     return one ? launch_chain_wt<WT, 1, 1, 1>(a, s) : launch_chain_wt<WT, 1, 1, 2>(a, s);

@@ -90,6 +90,7 @@ struct ChainArgs {
   void *y;                  // [T, h] act dtype
   int32_t T, h, act_f32;
   int32_t max_units;        // the most units a step of T tokens can have (<= kMaxChainUnits)
+  int32_t max_steps;        // the most K steps their concatenation can have
 };
 
 struct ZsumArgs {

@@ -165,6 +165,24 @@ def test_fused_down_row_blocks(hidden, w_dtype, T):
     check_case(Case(cfg, T, seed=60 + T))
 
 
+@pytest.mark.parametrize("hidden,w_dtype,T,kw", [
+    (256, "f32", 1, dict(d_shared=640)), (256, "f32", 1, dict(d_shared=704)),
+    (1024, "bf16", 1, dict(d_shared=512, d_private=0)), (1024, "fp8", 2, dict(d_private=128)),
+    (2048, "bf16", 20, dict(n_experts=4, n_depts=2, d_shared=512, d_private=0)),
+    (2048, "fp8", 24, dict(n_experts=4, n_depts=2, d_shared=512, d_private=128)),
+    (512, "f32", 17, dict(n_experts=2, n_depts=1, d_shared=1472, d_private=0)),
+    (512, "f32", 17, dict(n_experts=2, n_depts=1, d_shared=1536, d_private=0))])
+def test_fused_down_few_steps(hidden, w_dtype, T, kw):
+    """Narrow layers on both sides of the 24 K steps from which the fused down
+    kernel takes 8-row blocks (d_shared 640 | 704: 22 | 24 steps, 1472 | 1536:
+    23 | 24), with waves that get one step or none, one and two token tiles."""
+    act = "f32" if w_dtype == "f32" else "bf16"
+    cfg = small(hidden=hidden, w_dtype=w_dtype, act_dtype=act, **kw)
+    fused = 4 if T <= 4 else 5
+    assert D.deamoe_trace_points(D.make_config(cfg, T), T) == fused
+    check_case(Case(cfg, T, seed=110 + T))
+
+
 @pytest.mark.parametrize("d_shared,T", [(640, 6), (1088, 5), (1152, 5)])
 def test_fused_down_narrow_steps(d_shared, T):
     """Layers narrower than 2048 above 4 tokens: fused while a step has at
