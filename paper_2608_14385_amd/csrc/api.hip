@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -279,8 +280,7 @@ constexpr int kDownRows = 2 * kTile;
 
 // Waves sharing one down-projection tile.  The SLICE form packs several
 // short private tiles per work item and keeps whole tiles per wave, with K
-// split over two waves up to two tokens, where the batch leaves few work
-// items, and on layers narrower than 4096 (long contractions only,
+// split over two waves on layers narrower than 4096 (long contractions only,
 // down_split_k_of);
 // the FACTORED form (every contraction d long) splits K four ways up to 8
 // tokens and two ways up to 32 (64 where h >= 4096), while the batch leaves
@@ -290,7 +290,7 @@ constexpr int kDownRows = 2 * kTile;
 // 698.6, Kimi-K2 852.2 -> 846.2, Baseline-7B 71.5 -> 70.2; Qwen3 and
 // DeepSeek-V2, d = 1536, were even either way).
 int down_ks_of(const deamoe_config &c, int T) {
-  if (c.form == DEAMOE_FORM_SLICE) return T <= 2 || c.hidden < 4096 ? 2 : 1;
+  if (c.form == DEAMOE_FORM_SLICE) return c.hidden < 4096 ? 2 : 1;
   if (T <= 8) return 4;
   if (T <= 16 && c.d_shared >= 2048) return 4;
   if (T <= 16 && c.d_shared < 1024) return 1;
@@ -299,18 +299,53 @@ int down_ks_of(const deamoe_config &c, int T) {
 }
 
 
+// Time of a narrow SLICE down stage as its launch shape bounds it: rounds of
+// workgroups over the CUs, times the K steps of the longest wave, with the
+// units and token groups that uniform routing gives.  split: contractions
+// from kSplitK on are split over two waves.
+constexpr int kSplitK = 512, kLongK = 2048, kCUs = 256;
+double narrow_down_time(const deamoe_config &c, int T, bool split) {
+  const double m = c.n_depts, n = c.n_experts, gt = kTile * down_ntt_of(c, T);
+  double waves = 0;
+  int steps = 0;
+  auto add = [&](int K, double units, double tokens) {
+    if (K == 0) return;
+    const double groups = std::max(1.0, tokens / gt + 0.3);   // a unit's token groups vary
+    const int tiles = c.hidden / kDownRows, t = wave_tiles(K, kDownRows);
+    const bool two = split && K >= kSplitK;
+    waves += units * groups * (two ? 2 * tiles : (tiles + t - 1) / t);
+    steps = std::max(steps, (two ? K / 2 : t * K) / kstep_of(c.w_dtype));
+  };
+  double dk = m * (1 - std::pow(1 - 1 / m, c.top_k));   // departments of a token
+  if (c.top_k_dept) dk = std::min(dk, (double)c.top_k_dept);
+  add(c.d_shared, m * (1 - std::pow(1 - dk / m, T)), T * dk / m);
+  add(c.d_private, n * (1 - std::pow(1 - c.top_k / n, T)), T * c.top_k / n);
+  add(c.d_shared_expert, 1, T);
+  return std::ceil(1.03 * waves / 4 / kCUs) * steps;
+}
+
 // Shortest contraction that the K split of a down stage is for.  Layers
 // narrower than 4096 have few tiles, and without a split one wave streams all
 // K steps of a tile (22 in the 7B-class shared expert, the launch's critical
-// path); their short private contractions keep whole tiles per wave, several
-// to an item, which the split would leave waves without work.  Same-process
-// A/B against no split, us per step: the 7B-class layer 80.7 -> 69.5 at 25
-// tokens, 81.6 -> 76.5 at 40, 95.6 -> 87.4 at 61, 120.1 -> 114.1 at 128; the
-// 256-wide fp32 layer 45.4 -> 39.5 at 40.  Wider layers were even (the
-// DeepSeek-V3 shape 784.3 -> 784.3 at 64) or slower (fp8 404.7 -> 407.3 at
-// 45) and keep whole tiles.
+// path): from kLongK on the split always pays, and the layer's other units
+// are split with it.  Against no split, us per step: the 7B-class layer 80.7
+// -> 69.5 at 25 tokens, 81.6 -> 76.5 at 40, 95.6 -> 87.4 at 61, 120.1 -> 114.1
+// at 128.  Where every contraction is shorter, the private units' waves hold
+// several tiles and stream up to 1024 columns each anyway, so that a split
+// may only add workgroups: it is made unless narrow_down_time grows with it.
+// Step times, us, without the split | with it, for 8 departments and 64
+// experts of private 256: 1024 columns, 1024 wide 52.0 | 54.9 at 25 tokens,
+// 1536 wide 49.3 | 52.4 at 8 but 73.0 | 69.3 at 24; fp32, 1152 columns, 1920
+// wide 76.9 | 84.4 at 8; no private units, 512 columns, 512 wide 31.1 | 28.2 at
+// 5; the 256-wide fp32 layer 41.9 | 35.6 at 25.  Over 730 such pairs of shape
+// and batch, all types, none is slower than it was before there was a split;
+// 56 are more than 1 % (8 % at most) slower than the better form would be.
+// Wider layers were even (the DeepSeek-V3 shape 784.3 -> 784.3 at 64)
+// or slower with the split (fp8 404.7 -> 407.3 at 45) and keep whole tiles.
 int down_split_k_of(const deamoe_config &c, int T) {
-  return c.form == DEAMOE_FORM_SLICE && T > 2 ? 512 : 0;
+  if (c.form != DEAMOE_FORM_SLICE || down_ks_of(c, T) == 1) return 0;
+  if (std::max({c.d_shared, c.d_private, c.d_shared_expert}) >= kLongK) return kSplitK;
+  return narrow_down_time(c, T, false) < narrow_down_time(c, T, true) ? kLongK : kSplitK;
 }
 
 // Down projections and combine fused into one kernel (the SLICE down stage,
@@ -456,7 +491,7 @@ void fill_route_args(RouteArgs &a, const deamoe_config &c, int T, const void *x,
   a.plan = plan;
   a.down_rows = kDownRows;
   a.down_ks = down_ks_of(c, T);
-  a.down_split_k = down_split_k_of(c, T);
+  a.down_split_k = use_chain(c, T) ? 0 : down_split_k_of(c, T);   // no separate stage
   a.wave_tokens = kTile * (c.form == DEAMOE_FORM_FACTORED ? dept_ntt_of(c, T) : wave_ntt_of(c, T));
   a.wave_tokens_e = kTile * wave_ntt_of(c, T);
   a.wave_tokens_b = kTile * down_ntt_of(c, T);

@@ -48,6 +48,13 @@ __device__ inline int unit_epi(int f) { return f & 3; }
 __device__ inline int unit_out_f32(int f) { return f >> 2 & 1; }
 __device__ inline int unit_tpg(int f) { return f >> 3; }
 
+// Row tiles of `rows` rows that a wave holding whole tiles of a K-long
+// contraction takes: several of a short one, so that it streams enough bytes.
+__host__ __device__ inline int wave_tiles(int K, int rows) {
+  const int t = 2048 * kTile / (rows * K);
+  return t < 1 ? 1 : t > 8 ? 8 : t;
+}
+
 // One unit of the fused down projection and combine (at most 32 tokens): the
 // [R, K] down matrix w (fp8: block scales s) applied to
 // the unit's gate/up outputs `in` ([members, K], one row per member token in

@@ -219,16 +219,16 @@ __device__ inline void put_chain(gmem<ChainUnit> *U, const void *w, const float 
 }
 
 // Row tiles of a stage's work items.  A wave that holds whole tiles (K not
-// split) takes several of a short contraction, so that it streams enough
-// bytes.  With a K split over ks waves an item is one tile, except in units
-// whose K is shorter than split_k: there each wave takes tiles of its own.
+// split) takes wave_tiles of them.  With a K split over ks waves an item is
+// one tile, except in units whose K is shorter than split_k: there each wave
+// takes tiles of its own.
 struct ItemTiles {
   int item;   // tiles of a work item
   int flag;   // tiles of a wave for unit_flags, 0: the item's waves share its K steps
 };
 __device__ inline ItemTiles tiles_per_item(int K, int rows, int ks, int split_k) {
   if (ks > 1 && K >= split_k) return {1, 0};
-  int t = max(1, min(8, 2048 * kTile / (rows * K)));
+  int t = wave_tiles(K, rows);
   // fp8: a wave's block scales, (t * rows / 128 + 1) scale rows of K / 128,
   // fit the 64-entry window of a work item
   while (t > 1 && (t * rows / 128 + 1) * (K / 128) > 64) --t;

@@ -727,3 +727,19 @@ def test_narrow_down_split(hidden, w_dtype, T, d_shared, d_private, d_se):
     cfg = small(hidden=hidden, w_dtype=w_dtype, act_dtype=act, d_shared=d_shared,
                 d_private=d_private, d_shared_expert=d_se, n_experts=40, top_k=3)
     check_case(Case(cfg, T, seed=100 + T, bias="zipf"))
+
+
+@pytest.mark.parametrize("hidden,w_dtype,T,d_shared,d_private", [
+    (1536, "bf16", 8, 1024, 256), (1536, "bf16", 24, 1024, 256), (1024, "bf16", 33, 512, 256),
+    (2048, "bf16", 128, 1152, 128), (1920, "fp8", 8, 1152, 128), (1024, "f32", 25, 1024, 256),
+    (1536, "f32", 57, 512, 64), (512, "bf16", 5, 2048, 256)])
+def test_narrow_down_whole_tiles(hidden, w_dtype, T, d_shared, d_private):
+    """Narrow layers without a shared expert, where the K split depends on the
+    workgroups it adds: stages of whole tiles only (1536 wide at 8 tokens, 1024
+    at 25 and 33, 1920 at 8, 2048 at 128) and split ones (1536 at 24 and 57, 512
+    with 2048 columns), tile counts that are no multiple of a wave's tiles."""
+    act = "f32" if w_dtype == "f32" else "bf16"
+    cfg = small(hidden=hidden, w_dtype=w_dtype, act_dtype=act, d_shared=d_shared,
+                d_private=d_private, n_experts=64, n_depts=8, top_k=6)
+    assert D.deamoe_trace_points(D.make_config(cfg, T), T) == 6
+    check_case(Case(cfg, T, seed=120 + T))
