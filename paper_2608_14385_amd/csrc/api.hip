@@ -255,9 +255,19 @@ int slice_gate_up_ks_of(int T) { return T > kChainT ? 2 : 4; }
 // at 32, 156.7 -> 122.7 -> 97.4 at 64; DeepSeek-V2 (5120) two -> four 50.2 ->
 // 56.0 at 40, 69.9 -> 65.8 at 64; Baseline-7B even at 32 and 64 with two, 9.0
 // -> 12.2 at 64 with four.
+// fp8 keeps one tile on layers narrower than 4096 and, until four pay, above
+// 40 tokens (its two-tile kernel double-buffers the operand); fp32 keeps one up
+// to 24 tokens and two above 80 (its matrix products, not the rows, take the
+// time there).  Step time over that of the form left: fp8 two tiles -> one,
+// Baseline-7B 0.97 at 28 and 64 tokens, Qwen3 0.97 at 64 but 1.01 at 28; fp32
+// four -> two, 7168 wide, d = 1024, 0.90 at 96 but 1.09 at 65, 5120 wide, d =
+// 768, 0.87 at 128; fp32 two -> one 0.98 to 1.01 at 17 to 24 tokens, up to 1.07
+// from 28.
 int dept_ntt_of(const deamoe_config &c, int T) {
-  if (T <= kTile) return 1;
-  return (T > 48 && c.hidden >= 5120) || (T > 64 && c.hidden >= 4096) ? 4 : 2;
+  const bool f32 = c.w_dtype == DEAMOE_F32, fp8 = c.w_dtype == DEAMOE_FP8_E4M3_B128;
+  if (T <= (f32 ? 24 : kTile)) return 1;
+  if ((T > 48 && c.hidden >= 5120) || (T > 64 && c.hidden >= 4096)) return f32 && T > 80 ? 2 : 4;
+  return fp8 && (T > 40 || c.hidden < 4096) ? 1 : 2;
 }
 int dept_groups_max(const deamoe_config &c, int T) {
   const int gt = kTile * dept_ntt_of(c, T);

@@ -703,11 +703,14 @@ def test_work_items(d_private, T, cfg_kw):
     (512, "bf16", 17, {}), (512, "f32", 33, {}), (1024, "fp8", 50, {}),
     (4096, "bf16", 64, {}), (4096, "bf16", 65, dict(d_shared_expert=128)),
     (5120, "bf16", 48, {}), (5120, "f32", 49, {}), (5120, "fp8", 128, dict(d_shared_expert=256)),
-    (4096, "bf16", 128, dict(sigma="rmsnorm", top_k=4, top_k_dept=2))])
+    (4096, "bf16", 128, dict(sigma="rmsnorm", top_k=4, top_k_dept=2)),
+    (4096, "fp8", 40, {}), (4096, "fp8", 41, {}), (5120, "fp8", 48, {}), (4096, "fp8", 65, {}),
+    (512, "fp8", 128, {}), (4096, "f32", 24, {}), (4096, "f32", 25, {}), (4096, "f32", 80, {}),
+    (5120, "f32", 81, {})])
 def test_factored_department_tiles(hidden, w_dtype, T, cfg_kw):
     """The FACTORED department gate/up with one, two and four token tiles:
-    the batches and widths where the rule changes, departments of more than
-    one token group beside nearly empty ones (skewed), the shared expert."""
+    the batches, widths and types where the rule changes, departments of more
+    than one token group beside nearly empty ones (skewed), the shared expert."""
     act = "f32" if w_dtype == "f32" else "bf16"
     cfg = small(form="factored", hidden=hidden, d_shared=128, d_private=0, w_dtype=w_dtype,
                 act_dtype=act, **cfg_kw)
