@@ -98,73 +98,65 @@ void grouped_gemm_wide_kernel(GemmStage st) {
   grouped_gemm_body<WT, NW, NTT, KS, false, PAIR, true>(st);
 }
 
-// mode: GemmMode; row pairs exist for NTT <= 2 only (the host picks them so).
-// three: two-token-tile gate/up pairs run at three waves per SIMD.
-template <int WT, int NW, int NTT, int KS>
+// Launch of the stage's kernel, for the forms the host's rules pick (any other
+// combination is an error).  three: two-token-tile gate/up pairs run at three
+// waves per SIMD.
+template <int WT, int NTT, int KS>
 static hipError_t launch_gemm(const GemmStage &st, int mode, int max_tiles, int grid_cap,
                               bool three, hipStream_t s) {
   constexpr int TPB = 4 / KS;
   int grid = (max_tiles + TPB - 1) / TPB;
   grid = grid < 1 ? 1 : (grid > grid_cap ? grid_cap : grid);
-  constexpr bool FP8 = WT == WT_FP8;
-  auto plain = [&](auto k) {
+  auto run = [&](auto k) {
     hipLaunchKernelGGL(k, dim3(grid), dim3(256), 0, s, st);
     return hipGetLastError();
   };
-  if constexpr (NTT == 4) {   // four tiles: gate/up with a two-wave K split, row pairs without
-    if constexpr (KS == 2) {
-      if (mode == GEMM_PLAIN) return plain(grouped_gemm_wide_kernel<WT, NW, NTT, KS, false>);
-    } else if constexpr (KS == 1 && WT != WT_FP8) {
-      if (mode == GEMM_PAIR) return plain(grouped_gemm_wide_kernel<WT, NW, NTT, KS, true>);
-    }
-    return hipErrorInvalidValue;
-  }
-  if constexpr (NW == 2) {
-    if (mode == GEMM_SPLIT) {
-      if constexpr (NTT == 1)
-        return plain(grouped_gemm_occ3_kernel<WT, NW, NTT, KS, true, false, true>);
-      else   // two token tiles would spill at three waves per SIMD (no stage uses them)
-        return plain(grouped_gemm_kernel<WT, NW, NTT, KS, true, false>);
-    }
-    if (mode == GEMM_PAIR) {
-      if constexpr (NTT == 2)
-        return plain(grouped_gemm_occ3_kernel<WT, NW, NTT, KS, false, true, true>);
-      else if constexpr (NTT == 1)
-        return plain(grouped_gemm_kernel<WT, NW, NTT, KS, false, true>);
-      return hipErrorInvalidValue;   // row pairs are built for up to two token tiles
-    }
-    if constexpr (NTT == 2 && KS > 1) {
-      if constexpr (FP8)
-        return plain(grouped_gemm_occ3_kernel<WT, NW, NTT, KS, false, false, KS == 2>);
+  if (mode == GEMM_SPLIT) {
+    if constexpr (NTT == 1 && KS <= 2)
+      return run(grouped_gemm_occ3_kernel<WT, 2, NTT, KS, true, false, true>);
+  } else if (mode == GEMM_PAIR) {
+    if constexpr (NTT == 1)
+      return run(grouped_gemm_kernel<WT, 2, NTT, KS, false, true>);
+    else if constexpr (NTT == 2 && KS <= 2)
+      return run(grouped_gemm_occ3_kernel<WT, 2, NTT, KS, false, true, true>);
+    else if constexpr (NTT == 4 && KS == 1 && WT != WT_FP8)
+      return run(grouped_gemm_wide_kernel<WT, 2, NTT, KS, true>);
+  } else {
+    if constexpr (NTT == 1 && KS == 4) {
+      return run(grouped_gemm_kernel<WT, 2, NTT, KS, false, false>);
+    } else if constexpr (NTT == 2 && KS >= 2) {
+      if constexpr (WT == WT_FP8)
+        return run(grouped_gemm_occ3_kernel<WT, 2, NTT, KS, false, false, KS == 2>);
       else if (three)
-        return plain(grouped_gemm_occ3_kernel<WT, NW, NTT, KS, false, false, true>);
+        return run(grouped_gemm_occ3_kernel<WT, 2, NTT, KS, false, false, true>);
+      else
+        return run(grouped_gemm_kernel<WT, 2, NTT, KS, false, false>);
+    } else if constexpr (NTT == 4 && KS == 2) {
+      return run(grouped_gemm_wide_kernel<WT, 2, NTT, KS, false>);
     }
   }
-  return plain(grouped_gemm_kernel<WT, NW, NTT, KS, false, false>);
+  return hipErrorInvalidValue;
 }
 
-// Token tiles per wave: 1, 2, or 4 with a K split over 2 waves (larger
-// token sets are split into groups).
-template <int WT, int NW, int KS>
+// Token tiles per wave (larger token sets are split into groups) and K split.
+template <int WT, int KS>
 static hipError_t dispatch_ntt(const GemmStage &st, int mode, int ntt, int max_tiles, int cap,
                                bool three, hipStream_t s) {
   switch (ntt) {
-    case 1: return launch_gemm<WT, NW, 1, KS>(st, mode, max_tiles, cap, three, s);
-    case 2: return launch_gemm<WT, NW, 2, KS>(st, mode, max_tiles, cap, three, s);
-    case 4:   // gate/up with a K split over 2 waves, row pairs without one
-      if constexpr (KS <= 2) return launch_gemm<WT, NW, 4, KS>(st, mode, max_tiles, cap, three, s);
-      return hipErrorInvalidValue;
+    case 1: return launch_gemm<WT, 1, KS>(st, mode, max_tiles, cap, three, s);
+    case 2: return launch_gemm<WT, 2, KS>(st, mode, max_tiles, cap, three, s);
+    case 4: return launch_gemm<WT, 4, KS>(st, mode, max_tiles, cap, three, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-template <int WT, int NW>
+template <int WT>
 static hipError_t dispatch_ks(const GemmStage &st, int mode, int ntt, int ks, int max_tiles,
                               int cap, bool three, hipStream_t s) {
   switch (ks) {
-    case 1: return dispatch_ntt<WT, NW, 1>(st, mode, ntt, max_tiles, cap, three, s);
-    case 2: return dispatch_ntt<WT, NW, 2>(st, mode, ntt, max_tiles, cap, three, s);
-    default: return dispatch_ntt<WT, NW, 4>(st, mode, ntt, max_tiles, cap, three, s);
+    case 1: return dispatch_ntt<WT, 1>(st, mode, ntt, max_tiles, cap, three, s);
+    case 2: return dispatch_ntt<WT, 2>(st, mode, ntt, max_tiles, cap, three, s);
+    default: return dispatch_ntt<WT, 4>(st, mode, ntt, max_tiles, cap, three, s);
   }
 }
 
@@ -172,9 +164,9 @@ hipError_t launch_grouped_gemm(const GemmStage &st, int wtype, int nw, int mode,
                                int ks, int max_tiles, int grid_cap, hipStream_t s, bool three) {
   if (nw != 2) return hipErrorInvalidValue;   // every stage streams two matrices or a row pair
   switch (wtype) {
-    case WT_F32: return dispatch_ks<WT_F32, 2>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
-    case WT_BF16: return dispatch_ks<WT_BF16, 2>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
-    default: return dispatch_ks<WT_FP8, 2>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
+    case WT_F32: return dispatch_ks<WT_F32>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
+    case WT_BF16: return dispatch_ks<WT_BF16>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
+    default: return dispatch_ks<WT_FP8>(st, mode, ntt, ks, max_tiles, grid_cap, three, s);
   }
 }
 

@@ -104,10 +104,4 @@ constexpr float kRmsEps = 1e-6f;
 
 __device__ inline int lane_id() { return __lane_id(); }
 
-// Streaming 16-byte load that should not displace reusable lines in the caches.
-__device__ inline u32x4 load_stream16(const void *p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-}
-__device__ inline u32x4 load16(const void *p) { return *reinterpret_cast<const u32x4 *>(p); }
-
 }  // namespace deamoe

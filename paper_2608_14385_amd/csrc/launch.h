@@ -9,7 +9,6 @@ namespace deamoe {
 constexpr int kRouteThreads = 1024;
 constexpr int kMaxT = DEAMOE_MAX_TOKENS;
 constexpr int kMaxK = DEAMOE_MAX_TOPK;
-constexpr int kMaxTK = kMaxT * kMaxK;
 constexpr int kMaxN = DEAMOE_MAX_EXPERTS;
 constexpr int kMaxM = 1024;
 constexpr int kMaxMGrouped = 64;   // departments when top_k_dept > 0
