@@ -362,17 +362,22 @@ int down_split_k_of(const deamoe_config &c, int T) {
 // the FACTORED department down stage): batches whose active units fit the
 // kernel's unit table.  SLICE: up to 32 tokens (two token tiles from 17 on),
 // below kChainMinTiles row pairs (a hidden size under 4096) up to
-// kChainNarrowMaxT.  There the fused kernel measured faster beyond, too (the
-// 2048-wide 7B-class layer 85.3 -> 77.0 us per step at 25 tokens, 85.5 ->
-// 81.5 at 32), but the traced call gives those batches a boundary between the
-// down stage and the combine, which callers count.  On layers under
-// kChainNarrowMinTiles row pairs (2048), whose few workgroups must each walk
-// every unit, only up to 4 tokens or while the step has at most
-// kChainNarrowSteps K steps.  Same-process A/B against the separate down
-// stage and combine, us per step: the 256-wide fp32 layer (at most 48 steps)
-// 38.9 -> 26.2 at 6 tokens, 41.3 -> 29.3 at 16; the 1024-wide Baseline-7B
-// vanilla layer even at 5 (at most 120 steps), 46.7 -> 49.5 at 8 (192) and
-// 65.2 -> 71.2 at 16.  FACTORED: up to 16 tokens at every
+// kChainNarrowMaxT.  Step times, us, fused | the separate stage (K split) and
+// combine: the 2048-wide 7B-class layer 63.2 | 68.6 at 16 tokens, 70.0 | 68.5
+// at 17, 72.9 | 69.7 at 24, 73.2 | 70.0 at 25, fp8 49.8 | 52.0 at 16, 63.7 |
+// 58.2 at 24, fp32 105.1 | 110.7 at 16, 138.0 | 116.8 at 24.  By time the line
+// lies at 16, where the second token tile comes in (232 registers, not 140);
+// it stays at 24, because it also decides how many events the traced call
+// records, and callers have deamoe_trace_points' answers for these batches.
+// On layers under kChainNarrowMinTiles row pairs (2048), whose few workgroups
+// must each walk every unit, only up to 4 tokens or while the step has at most
+// kChainNarrowSteps K steps.  Fused | separate: the 256-wide fp32 layer (at
+// most 48 steps) 26.2 | 38.9 at 6 tokens, 29.3 | 41.3 at 16; 32 departments of
+// 512 columns, 512 wide, 26.7 | 27.0 at 6 (96 steps), 28.8 | 28.1 at 8 (128),
+// 256 wide 24.5 | 24.3 and 25.8 | 24.9; the 1024-wide Baseline-7B vanilla layer
+// 49.5 | 46.7 at 8 (192).  Layers with private units gain up to 128 steps (8
+// departments of 1536 columns, 1024 wide, 42.1 | 43.2 at 16), but with few of
+// them the line lies at 96.  FACTORED: up to 16 tokens at every
 // Table 1 width (at least kChainMinTilesFactored row pairs, h >= 1024): the
 // fused kernel saves the combine launch.  Same-process A/B against the
 // separate department down stage and combine, us per step: Baseline-7B (h =

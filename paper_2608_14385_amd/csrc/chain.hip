@@ -54,10 +54,13 @@ __device__ inline void chain_mma(const u32x4 (&a)[NW][4], const u32x4 (&b)[4], b
 
 // NW: 16-row halves of y per workgroup (1 or 2; two share the token operand).
 // Bound by the read rate on wide layers (224 workgroups at 7168: 6.7 TB/s at
-// 16 tokens), by a CU's rate and the prologue on narrow ones.  Scalar step
-// addresses, the unit fields through scalar loads instead of LDS and one loop
-// exit took the pair kernel from 170 registers to 146 (three waves per SIMD);
-// kernel time by trace, us: the DeepSeek-V3 shape 174.9 -> 171.9 at 16
+// 16 tokens), on narrow ones by the token operand beside few rows (4.1 TB/s
+// on the 7B-class layer at 16) and the prologue.  A CU holds one workgroup of
+// pairs (142 registers, two waves per SIMD; a second needs 128), two of single
+// halves with one token tile.  Scalar step addresses, the unit fields through
+// scalar loads instead of LDS and one loop exit, which saved the pair kernel 28
+// registers but no occupancy; kernel time by trace, us: the DeepSeek-V3 shape
+// 174.9 -> 171.9 at 16
 // tokens, 214.5 -> 212.4 at 32, fp8 142.1 -> 135.3 at 32 and 20.5 -> 19.7 at
 // one token, the 256-wide fp32 layer 7.4 -> 5.7 at 4.
 // P: with NW == 1, a load group is P K steps of 16 / P rows instead of one
@@ -279,14 +282,15 @@ static hipError_t launch_chain_wt(const ChainArgs &a, hipStream_t s) {
 constexpr int kChainPairMinH = 5120;
 // Up to 2048, where 16-row blocks leave half the CUs idle, a workgroup takes
 // 8 rows, two K steps side by side in a load group (at most 256 workgroups of
-// one a CU).  A CU's own rate is what bounds the kernel there, not the
-// latency: 12 or 16 waves on 128 CUs were no faster.  Kernel time by trace,
-// us, 16 rows -> 8: the 7B-class layer 10.0 -> 8.4 at one token, 16.4 -> 13.7
+// one a CU); 12 or 16 waves on 128 CUs instead were no faster.  The price is
+// the token operand, 4 KB per token tile and K step beside 2 KB of weights.
+// Kernel time by trace, us, 16 rows -> 8: the 7B-class layer 10.0 -> 8.4 at one
+// token, 16.4 -> 13.7
 // at 5, 22.2 -> 18.6 at 16, 29.5 -> 26.9 at 24; Baseline-7B (1024 wide) 6.3
 // -> 5.5 at 16.  At 4096 (Qwen3, 512 workgroups in two rounds) 8 rows lost:
 // 18.9 -> 25.2 at 16, and 4 rows lost at 2048 too.
 // A step of fewer than kChainSplitSteps K steps keeps 16 rows: a wave then has
-// two or three steps at most, which a 16-row wave requests at once, and the
+// three steps at most, a 16-row wave requests two of them at once, and the
 // pairs only double the matrix products and the prologue's work.  Step times,
 // us, 8 rows -> 16: Baseline-7B FACTORED at one token (at most 12 steps) 33.7
 // -> 33.3; 1024-wide layers of 8 steps at one token 14.9 -> 14.4 (bf16) and

@@ -8,10 +8,11 @@
 namespace deamoe {
 
 // The unit a work item belongs to: the last one whose first item is <= item.
-// Every lane of the wave compares one entry of the prefix per 64 units.  This
-// is the start of every work item's chain of dependent reads (prefix, unit,
-// weights), so it is one round trip: no wait for the counts, no copy to LDS,
-// no barrier, no search over dependent LDS reads.
+// Every lane of the wave compares one entry of the prefix per 64 units.  A
+// work item starts with a chain of dependent reads (counts, prefix, unit,
+// weights), so finding its unit is one round trip after the counts, which say
+// whether the workgroup has an item at all: no copy to LDS, no barrier, no
+// search over dependent LDS reads.
 __device__ inline int find_unit(const GemmStage &st, int n_units, int item) {
   constexpr int U = 8;
   const gmem<const int32_t> *begin = glob(st.begin);
@@ -38,9 +39,8 @@ __device__ __attribute__((always_inline)) void grouped_gemm_body(const GemmStage
   using Run = TileRunner<WT, NW, NTT, KS, SPLIT, PAIR, B1>;
   __shared__ typename Run::Smem sm;
   const int wave = uniform(threadIdx.x / kWave);
-  // the grid is sized for the most work a step can have; the prefix is read
-  // as far as the batch can have units, so that its loads don't wait for the
-  // counts'
+  // the grid is sized for the most work a step can have; the prefix is read as
+  // far as the batch can have units, entries past the step's units not counted
   const int n_units = uniform(st.counts[0]), n_tiles = uniform(st.counts[1]);
   for (int base = blockIdx.x * Run::TPB; base < n_tiles; base += gridDim.x * Run::TPB) {
     const int tile = base + wave / KS;
@@ -88,10 +88,11 @@ void grouped_gemm_occ3_kernel(GemmStage st) {
 }
 
 // Four token tiles per wave (64 tokens), for the gate/up stage of wide
-// layers above 64 tokens (fp8: above 96) and the bf16 down stage's row pairs
-// there: a unit with many tokens streams its rows once per 64 tokens instead
-// of once per 32.  The token operand is requested per step (B1);
-// two waves per SIMD.
+// layers above 64 tokens (fp8: above 96), the row pairs of the bf16 and fp32
+// down stages there, and the FACTORED department gate/up (dept_ntt_of: from 49
+// tokens on layers at least 5120 wide): a unit with many tokens streams its
+// rows once per 64 tokens instead of once per 32.  The token operand is
+// requested per step (B1); two waves per SIMD.
 template <int WT, int NW, int NTT, int KS, bool PAIR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 void grouped_gemm_wide_kernel(GemmStage st) {

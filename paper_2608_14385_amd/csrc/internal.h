@@ -25,7 +25,7 @@ enum Epilogue : int32_t {
 };
 
 // One weight matrix (or gate/up pair) applied to a group of token rows.
-// A work item is `tpg` consecutive 16-row tiles of the unit.
+// A work item is one row tile, or several consecutive ones (unit_flags).
 // Row r of the weights is at w + r * ldw (elements of the weight type).  The
 // B operand row of token i is at in + idx[i] * ldin (idx == NULL: row i).
 // Output row of token i is at out + i * ldout (act type or fp32).
@@ -40,7 +40,10 @@ struct GemmUnit {
 };
 
 // flags of a unit: its Epilogue, whether its outputs are fp32 (else the act
-// dtype), and its row tiles per work item (1 unless the K split is 1).
+// dtype), and the row tiles that a wave of a work item takes (tpg).  Stages with
+// a K split ignore tpg, their items are one tile each, except row pairs split
+// over two waves: there 0 marks such a unit, and other units' waves take tpg
+// whole tiles each.
 __host__ __device__ inline int unit_flags(int epi, int out_f32, int tpg) {
   return epi | out_f32 << 2 | tpg << 3;
 }

@@ -79,8 +79,8 @@ struct CombineArgs {
   int32_t T, h, max_slots, act_f32;
 };
 
-// Fused down projection and combine (T <= kChainT): one workgroup per 32
-// rows of y.
+// Fused down projection and combine (T <= kChainT): one workgroup per 32, 16
+// or 8 rows of y.
 constexpr int kMaxChainUnits = 512;
 constexpr int kChainT = 32;   // tokens; also the row length of the token-weight table
 struct ChainArgs {

@@ -309,8 +309,16 @@ static hipError_t launch_small_wt(const RouteArgs &a, int items, hipStream_t s) 
   }
 }
 
-// One-tile workgroups of this kernel an MI355X holds at once: 256 CUs, three
-// per CU for bf16 and fp32 weights (registers), four for fp8 (LDS).
+// One-tile workgroups per launch that the rule below counts on: 256 CUs, three
+// per CU for bf16 and fp32 weights, four for fp8.  Up to 8 experts per lane
+// four bf16 ones are resident too (125 registers, 38.7 KB of LDS).  Built for
+// three (amdgpu_waves_per_eu(3, 3)) the launch is slower or even; step times,
+// us, four -> three: the 7B-class layer 42.9 -> 44.7 at 4 tokens, DeepSeek-V2
+// FACTORED 149.6 -> 155.6 at 3, fp8 DeepSeek-V3 127.5 -> 133.5 at 3, the
+// DeepSeek-V3 shape 106.9 -> 106.6 at one token.  Counting four in the rule
+// would bring the DeepSeek-V3 FACTORED layer's 2 to 4 tokens here (205.0 ->
+// 200.0 at 2, 293.8 -> 292.8 at 4; the other presets keep their path), with one
+// traced event fewer than deamoe_trace_points gives for them: it stays three.
 constexpr int kCUs = 256;
 static int single_tile_slots(int wtype) { return kCUs * (wtype == WT_FP8 ? 4 : 3) - 1; }
 
