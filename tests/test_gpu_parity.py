@@ -156,13 +156,29 @@ def test_fused_down_combine(variant):
     (256, "bf16", 16), (2176, "bf16", 19), (2176, "fp8", 7), (4096, "f32", 2)])
 def test_fused_down_row_blocks(hidden, w_dtype, T):
     """The fused down kernel's row blocks: 8 rows with two K steps side by
-    side up to 2048, single 16-row halves from there.  Both token tiles, step
-    counts that leave waves without work (one unit of one step per expert at
-    T = 1) and ranges of odd length, a ragged shared expert."""
+    side up to 2048 (16 where a step has few K steps, as at T = 1), single
+    16-row halves from there.  Both token tiles, ranges of odd length, a ragged
+    shared expert."""
     act = "f32" if w_dtype == "f32" else "bf16"
     cfg = small(hidden=hidden, w_dtype=w_dtype, act_dtype=act, d_shared=384, d_private=128,
                 d_shared_expert=0 if T == 1 else 640, n_experts=24, top_k=3)
+    fused = 4 if T <= 4 else 5
+    assert D.deamoe_trace_points(D.make_config(cfg, T), T) == fused
     check_case(Case(cfg, T, seed=60 + T))
+
+
+@pytest.mark.parametrize("w_dtype,T,experts", [("bf16", 24, 1), ("f32", 12, 3), ("fp8", 24, 9)])
+def test_fused_down_idle_waves(w_dtype, T, experts):
+    """8-row blocks (a step can have 24 K steps) where routing leaves waves
+    without work: every token on the same expert, on one of three, of nine."""
+    act = "f32" if w_dtype == "f32" else "bf16"
+    cfg = small(hidden=512, w_dtype=w_dtype, act_dtype=act, n_experts=24, n_depts=24, top_k=1,
+                d_shared=128, d_private=0)
+    assert D.deamoe_trace_points(D.make_config(cfg, T), T) == 5
+    case = Case(cfg, T, seed=65)
+    case.logits = torch.zeros(T, 24, device="cuda")
+    case.logits[torch.arange(T), torch.arange(T) % experts + 5] = 1.0
+    check_case(case)
 
 
 @pytest.mark.parametrize("hidden,w_dtype,T,kw", [
@@ -183,13 +199,18 @@ def test_fused_down_few_steps(hidden, w_dtype, T, kw):
     check_case(Case(cfg, T, seed=110 + T))
 
 
-@pytest.mark.parametrize("d_shared,T", [(640, 6), (1088, 5), (1152, 5)])
+@pytest.mark.parametrize("d_shared,T", [(640, 6), (1088, 5), (1152, 5), (1216, 8), (1280, 8)])
 def test_fused_down_narrow_steps(d_shared, T):
     """Layers narrower than 2048 above 4 tokens: fused while a step has at
-    most 96 K steps (640: 56 at 6 tokens; 1088 and 1152: 82 and 86 at 5), the
-    separate stage beyond (d_private 512 below)."""
-    check_case(Case(small(d_shared=d_shared, d_private=64, d_shared_expert=256), T, seed=70))
-    check_case(Case(small(d_shared=d_shared, d_private=512, top_k=3), T, seed=71))
+    most 96 K steps (640: 56 at 6 tokens; 1088 and 1152: 82 and 86 at 5; 1216
+    and 1280: 96 and 100 at 8), the separate stage beyond (d_private 512
+    below)."""
+    cfg = small(d_shared=d_shared, d_private=64, d_shared_expert=256)
+    assert D.deamoe_trace_points(D.make_config(cfg, T), T) == (6 if d_shared == 1280 else 5)
+    check_case(Case(cfg, T, seed=70))
+    cfg = small(d_shared=d_shared, d_private=512, top_k=3)
+    assert D.deamoe_trace_points(D.make_config(cfg, T), T) == 6
+    check_case(Case(cfg, T, seed=71))
 
 
 @pytest.mark.parametrize("variant", ["f32_t128_se", "bf16_t128_se"])
