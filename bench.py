@@ -39,9 +39,9 @@ HBM_PEAK_GBPS = 8000.0
 #  - the average launch duration from a kernel-trace run of the default
 #    command (profiles/gate_up_dsv3_bf16_T16_kernel_trace.md), which excludes
 #    the launch gap that the benchmark's own events include.
-TRAFFIC_BYTES = 2341200282
-PROFILED_GATE_UP_US = 359.44
-TRAFFIC_SOURCES_SHA256 = "395db81b1c53e23bb0f22db2b00e3a8fa831a1e687a8f918626e92a1cb08a662"
+TRAFFIC_BYTES = 2341227725
+PROFILED_GATE_UP_US = 336.03
+TRAFFIC_SOURCES_SHA256 = "9219c5074e6e645dbd9950dedd72156872a9ccc266c7610b6ab2f086c26bc1d0"
 
 
 def library_sources_digest() -> str:
