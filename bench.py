@@ -40,8 +40,8 @@ HBM_PEAK_GBPS = 8000.0
 #    command (profiles/gate_up_dsv3_bf16_T16_kernel_trace.md), which excludes
 #    the launch gap that the benchmark's own events include.
 TRAFFIC_BYTES = 2341227725
-PROFILED_GATE_UP_US = 336.03
-TRAFFIC_SOURCES_SHA256 = "9219c5074e6e645dbd9950dedd72156872a9ccc266c7610b6ab2f086c26bc1d0"
+PROFILED_GATE_UP_US = 337.01
+TRAFFIC_SOURCES_SHA256 = "ef33088ef9d6c3ccd79a21a073f9660f458e69eda0e9576c44d19867158ae913"
 
 
 def library_sources_digest() -> str:

@@ -347,11 +347,11 @@ double narrow_down_time(const deamoe_config &c, int T, bool split) {
 // experts of private 256: 1024 columns, 1024 wide 52.0 | 54.9 at 25 tokens,
 // 1536 wide 49.3 | 52.4 at 8 but 73.0 | 69.3 at 24; fp32, 1152 columns, 1920
 // wide 76.9 | 84.4 at 8; no private units, 512 columns, 512 wide 31.1 | 28.2 at
-// 5; the 256-wide fp32 layer 41.9 | 35.6 at 25.  Over 730 such pairs of shape
+// 5; the 256-wide fp32 layer 41.9 | 35.6 at 25.  Over 680 such pairs of shape
 // and batch, all types, none is slower than it was before there was a split;
-// 56 are more than 1 % (8 % at most) slower than the better form would be.
-// Wider layers were even (the DeepSeek-V3 shape 784.3 -> 784.3 at 64)
-// or slower with the split (fp8 404.7 -> 407.3 at 45) and keep whole tiles.
+// one in 13 is more than 1 % (8 % at most) slower than the better form would
+// be.  Wider layers were even (the DeepSeek-V3 shape 784.3 -> 784.3 at 64) or
+// slower with the split (fp8 404.7 -> 407.3 at 45) and keep whole tiles.
 int down_split_k_of(const deamoe_config &c, int T) {
   if (c.form != DEAMOE_FORM_SLICE || down_ks_of(c, T) == 1) return 0;
   if (std::max({c.d_shared, c.d_private, c.d_shared_expert}) >= kLongK) return kSplitK;
